@@ -492,7 +492,8 @@ def main():
     cur, hist, nsel = attended_keys(w.seqlens, w.block_size, w.topk)
     flop = 4.0 * w.d * w.hq * (cur + hist)
     tflops = flop / (ms * 1e-3) / 1e12
-    hist_flop_step = 4.0 * w.d * w.hq * hist
+    # calls without an "attn_cur" phase run their current-block tiles in the same launch
+    hist_flop_step = 4.0 * w.d * w.hq * (hist if "attn_cur" in phases else hist + cur)
     hl, hms = phases.get("attn_hist", (0, 0.0))
     launches_per_step = hl / max(args.steps, 1)
     achieved = (hist_flop_step / launches_per_step) / (hms / hl * 1e-3) / 1e12 if hl else 0.0

@@ -5,9 +5,8 @@
 // moba_forward enqueues, on the caller's stream:
 //   pool -> [bf16: V^T pack] -> gate -> route (count, column scan, bin scan,
 //   scatter) -> per chunk of kv-heads: history attention, then current-block
-//   attention, then the merge of the history partials (bf16: a separate
-//   kernel working in place on the output; fp32: fused into the current-block
-//   kernel).
+//   attention (fp32: both in one launch), then the merge of the history
+//   partials, in place on the output.
 // Only the attention steps depend on the chunk; their workspace (the
 // partials: bf16 on the bf16 path, fp32 on the fp32 path) is what the
 // workspace cap limits.
@@ -774,22 +773,24 @@ moba_status moba_forward(const moba_tensor* q, const moba_tensor* k, const moba_
     a.g0 = g0;
     a.g1 = std::min(p.Hkv, g0 + nch);
     const int64_t e_chunk = pl->hist_per_head * p.G * (a.g1 - a.g0);
-    if (kh > 0 && e_chunk > 0) {
-      const int64_t grid = ceil_div(e_chunk, p.tile_rows) + (int64_t)(a.g1 - a.g0) * p.nblk_total;
-      Phase ph("attn_hist", stream);
-      MOBA_LAUNCH(in.bf16 ? launch_attn_hist_bf16(a, p, grid, stream)
-                          : launch_attn_hist_f32(a, p, grid, stream));
-    }
+    const int64_t hist_tiles =
+        kh > 0 && e_chunk > 0
+            ? ceil_div(e_chunk, p.tile_rows) + (int64_t)(a.g1 - a.g0) * p.nblk_total
+            : 0;
     if (in.bf16) {
-      { Phase ph("attn_cur", stream);
-        MOBA_LAUNCH(launch_attn_causal_bf16(false, a, p, stream)); }
-      if (kh > 0) {
-        Phase ph("merge", stream);
-        MOBA_LAUNCH(launch_merge_bf16(a, p, stream));
+      if (hist_tiles > 0) {
+        Phase ph("attn_hist", stream);
+        MOBA_LAUNCH(launch_attn_hist_bf16(a, p, hist_tiles, stream));
       }
+      Phase ph("attn_cur", stream);
+      MOBA_LAUNCH(launch_attn_causal_bf16(false, a, p, stream));
     } else {
-      Phase ph("attn_cur_merge", stream);
-      MOBA_LAUNCH(launch_attn_causal_f32(false, a, p, stream));
+      Phase ph("attn_hist", stream);  // and the current-block tiles
+      MOBA_LAUNCH(launch_attn_f32(a, p, hist_tiles, stream));
+    }
+    if (kh > 0) {
+      Phase ph("merge", stream);
+      MOBA_LAUNCH(launch_merge(in.bf16, a, p, stream));
     }
   }
   return MOBA_OK;
@@ -1055,7 +1056,7 @@ moba_status dense_forward_impl(const Inputs& in, const View& vo, moba_tensor* ls
   }
   { Phase ph("dense", stream);
     MOBA_LAUNCH(in.bf16 ? launch_attn_causal_bf16(true, a, p, stream)
-                        : launch_attn_causal_f32(true, a, p, stream)); }
+                        : launch_attn_f32(a, p, 0, stream)); }
   return MOBA_OK;
 }
 

@@ -120,10 +120,11 @@ struct AttnArgs {
 // (extra work-groups exit).  Causal tiles: a.ntiles x (g1 - g0) work-groups.
 hipError_t launch_attn_hist_bf16(const AttnArgs& a, const Problem& p, int64_t grid, hipStream_t st);
 hipError_t launch_attn_causal_bf16(bool dense, const AttnArgs& a, const Problem& p, hipStream_t st);
-hipError_t launch_attn_hist_f32(const AttnArgs& a, const Problem& p, int64_t grid, hipStream_t st);
-hipError_t launch_attn_causal_f32(bool dense, const AttnArgs& a, const Problem& p, hipStream_t st);
-// bf16 path: folds the history partials of chunk rows into out / lse in place.
-hipError_t launch_merge_bf16(const AttnArgs& a, const Problem& p, hipStream_t st);
+// fp32: the chunk's history tiles (at most hist_tiles, 0: none) and its causal
+// tiles in one launch.
+hipError_t launch_attn_f32(const AttnArgs& a, const Problem& p, int64_t hist_tiles, hipStream_t st);
+// Folds the history partials of chunk rows into out / lse in place.
+hipError_t launch_merge(bool bf16, const AttnArgs& a, const Problem& p, hipStream_t st);
 
 // ------------------------------------------------------------ device helpers
 // Largest s with key[s] <= x among sequences, skipping empty ones that share
