@@ -95,6 +95,28 @@ __device__ __forceinline__ void write_sel(int32_t* out, const int* id, int c, in
   for (int x = nh + 1; x < K; x++) out[x] = -1;
 }
 
+// The work-group's kept past blocks, counted per block in LDS (cnt: nb words
+// that no wave reads any more after the first barrier) and written to dst[nb].
+// Every thread of the work-group calls it.
+template <int KM>
+__device__ __forceinline__ void count_kept(int32_t* cnt, int nb, bool valid, const int* id, int c,
+                                           int K, int32_t* dst) {
+  __syncthreads();
+  for (int j = threadIdx.x; j < nb; j += 256) cnt[j] = 0;
+  __syncthreads();
+  if (valid) {
+    if (KM > 0 && c >= K) {
+#pragma unroll
+      for (int x = 0; x < KM; x++)
+        if (id[x] < c) atomicAdd(&cnt[id[x]], 1);
+    } else {
+      for (int j = 0; j < c; j++) atomicAdd(&cnt[j], 1);
+    }
+  }
+  __syncthreads();
+  for (int j = threadIdx.x; j < nb; j += 256) dst[j] = cnt[j];
+}
+
 // KM: capacity of the register list (>= topk - 1); KM == 0 selects every past
 // block (topk - 1 >= every row's number of past blocks).
 template <typename T, int KM>
@@ -102,7 +124,8 @@ __global__ __launch_bounds__(256) void gate_kernel(const T* __restrict__ q, int6
                                                    int64_t q_sh, const float* __restrict__ kbar,
                                                    const SeqInfo* __restrict__ seqs, Problem p,
                                                    int32_t* __restrict__ sel,
-                                                   float* __restrict__ scores, int nmax) {
+                                                   float* __restrict__ scores, int nmax,
+                                                   int32_t* __restrict__ gcount) {
   __shared__ float4 kb[kStage][kHeadDim / 4];
   const int g = blockIdx.y;
   const int s = find_seq(seqs, p.S, (int64_t)blockIdx.x, [](const SeqInfo& x) { return x.gate_off; });
@@ -170,6 +193,9 @@ __global__ __launch_bounds__(256) void gate_kernel(const T* __restrict__ q, int6
       }
     }
   }
+  if (gcount)
+    count_kept<KM>(reinterpret_cast<int32_t*>(kb), sq.nblk, valid, id, c, K,
+                   gcount + ((int64_t)g * p.gate_groups + blockIdx.x) * p.nblk_max);
   if (!valid) return;
   write_sel<KM>(sel + srow * K, id, c, K);
 }
@@ -230,7 +256,8 @@ template <int KM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KM <= 31 ? 2 : 1)))
 void gate_mfma_kernel(const __hip_bfloat16* __restrict__ q, int64_t q_st, int64_t q_sh,
                       const __hip_bfloat16* __restrict__ kterm, const SeqInfo* __restrict__ seqs,
-                      Problem p, int32_t* __restrict__ sel, float* __restrict__ scores, int nmax) {
+                      Problem p, int32_t* __restrict__ sel, float* __restrict__ scores, int nmax,
+                      int32_t* __restrict__ gcount) {
   __shared__ __attribute__((aligned(16))) __bf16 terms[3][kChunk][kTermRow];
   __shared__ __attribute__((aligned(16))) float st[4][64][kScoreRow];
   const int g = blockIdx.y;
@@ -422,6 +449,9 @@ void gate_mfma_kernel(const __hip_bfloat16* __restrict__ q, int64_t q_st, int64_
       __builtin_amdgcn_wave_barrier();
     }
   }
+  if (gcount)
+    count_kept<KM>(reinterpret_cast<int32_t*>(terms), sq.nblk, valid, li, c, K,
+                   gcount + ((int64_t)g * p.gate_groups + blockIdx.x) * p.nblk_max);
   if (!valid) return;
   write_sel<KM>(sel + srow * K, li, c, K);
 }
@@ -429,23 +459,23 @@ void gate_mfma_kernel(const __hip_bfloat16* __restrict__ q, int64_t q_st, int64_
 template <typename T, int KM>
 hipError_t launch_km(const void* q, int64_t q_st, int64_t q_sh, const float* kbar,
                      const __hip_bfloat16* kterm, const SeqInfo* seqs, const Problem& p,
-                     int32_t* sel, float* scores, int nmax, hipStream_t st) {
+                     int32_t* sel, float* scores, int nmax, int32_t* gcount, hipStream_t st) {
   dim3 grid((unsigned)p.gate_groups, p.Hkv);
   if constexpr (std::is_same<T, __hip_bfloat16>::value)
     gate_mfma_kernel<KM><<<grid, 256, 0, st>>>(static_cast<const T*>(q), q_st, q_sh, kterm, seqs,
-                                               p, sel, scores, nmax);
+                                               p, sel, scores, nmax, gcount);
   else
     gate_kernel<T, KM><<<grid, 256, 0, st>>>(static_cast<const T*>(q), q_st, q_sh, kbar, seqs, p,
-                                             sel, scores, nmax);
+                                             sel, scores, nmax, gcount);
   return hipGetLastError();
 }
 
 template <typename T>
 hipError_t launch_typed(const void* q, int64_t q_st, int64_t q_sh, const float* kbar,
                         const __hip_bfloat16* kterm, const SeqInfo* seqs, const Problem& p,
-                        int32_t* sel, float* scores, int nmax, hipStream_t st) {
+                        int32_t* sel, float* scores, int nmax, int32_t* gcount, hipStream_t st) {
   const int kh = p.topk - 1;
-#define MOBA_GATE_KM(n) launch_km<T, n>(q, q_st, q_sh, kbar, kterm, seqs, p, sel, scores, nmax, st)
+#define MOBA_GATE_KM(n) launch_km<T, n>(q, q_st, q_sh, kbar, kterm, seqs, p, sel, scores, nmax, gcount, st)
   if (kh >= p.nblk_max - 1) return MOBA_GATE_KM(0);
   if (kh <= 1) return MOBA_GATE_KM(1);
   if (kh <= 3) return MOBA_GATE_KM(3);
@@ -461,11 +491,11 @@ hipError_t launch_typed(const void* q, int64_t q_st, int64_t q_sh, const float* 
 
 hipError_t launch_gate(const void* q, bool bf16, int64_t q_st, int64_t q_sh, const float* kbar,
                        const __hip_bfloat16* kterm, const SeqInfo* seqs, const Problem& p,
-                       int32_t* sel, float* scores, int nmax, hipStream_t st) {
+                       int32_t* sel, float* scores, int nmax, int32_t* gcount, hipStream_t st) {
   if (p.gate_groups == 0) return hipSuccess;
   if (bf16)
-    return launch_typed<__hip_bfloat16>(q, q_st, q_sh, kbar, kterm, seqs, p, sel, scores, nmax, st);
-  return launch_typed<float>(q, q_st, q_sh, kbar, nullptr, seqs, p, sel, scores, nmax, st);
+    return launch_typed<__hip_bfloat16>(q, q_st, q_sh, kbar, kterm, seqs, p, sel, scores, nmax, gcount, st);
+  return launch_typed<float>(q, q_st, q_sh, kbar, nullptr, seqs, p, sel, scores, nmax, gcount, st);
 }
 
 }  // namespace moba

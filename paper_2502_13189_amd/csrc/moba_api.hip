@@ -274,6 +274,17 @@ void build_plan(const std::vector<int32_t>& cu, int Hq, int Hkv, int B, int topk
   p.hist_words = hw;
   pl->hist_per_head = hist;
   p.hist_entries = hist * Hq;
+  if (mode == kTilesCur && route_gate_counts(p)) {
+    // routing chunks of whole gate groups (hist_words keeps the workspace's size)
+    p.gate_counts = true;
+    p.route_rt = p.gate_tw * std::max(1, kRouteRows / (p.gate_tw * p.G));
+    rc = 0;
+    for (int s = 0; s < S; s++) {
+      pl->seqs[s].rc_off = (int32_t)rc;
+      rc += ceil_div(pl->seqs[s].len, p.route_rt);
+    }
+    p.route_chunks = rc;
+  }
 
   pl->tiles.clear();
   pl->ktiles.clear();
@@ -653,6 +664,8 @@ void forward_layout(const Problem& p, bool bf16, int kk, int nch, Bump* bp, FwdB
   b->o_part = bf16 ? (void*)bp->take<__hip_bfloat16>(rows * kh * kHeadDim)
                    : (void*)bp->take<float>(rows * kh * kHeadDim);
   b->lse_part = bp->take<float>(rows * kh);
+  // the gate's counts are done with before the first partial is written
+  b->rb.gcount = p.gate_counts ? static_cast<int32_t*>(b->o_part) : nullptr;
 }
 
 // Number of blocks and of history selections (route entries) of a batch:
@@ -763,8 +776,7 @@ moba_status moba_forward(const moba_tensor* q, const moba_tensor* k, const moba_
   }
   { Phase ph("gate", stream);
     MOBA_LAUNCH(launch_gate(in.q.data, in.bf16, in.q.st, in.q.sh, kbar, fb.kterm, d_seqs, p, sel,
-                            nullptr, 0,
-                            stream)); }
+                            nullptr, 0, rb.gcount, stream)); }
   if (kh > 0 && p.hist_entries > 0) {
     Phase ph("route", stream);
     MOBA_LAUNCH(launch_route(sel, d_seqs, p, rb, stream));
@@ -886,6 +898,8 @@ moba_status backward_impl(const moba_tensor* q, const moba_tensor* k, const moba
     b->ld = bp->take<float2>(p.T * p.Hq);
     b->rec = bp->take<int4>(routed ? p.hist_entries : 0);
     b->dq_part = bp->take<float>(routed ? (int64_t)nch * TG * kh * kHeadDim : 0);
+    // the gate's counts are done with before the first dQ partial is written
+    b->rb.gcount = p.gate_counts ? reinterpret_cast<int32_t*>(b->dq_part) : nullptr;
   };
   const size_t limit = workspace_limit();
   int nch = 0;
@@ -951,8 +965,7 @@ moba_status backward_impl(const moba_tensor* q, const moba_tensor* k, const moba
                                d_seqs, p, b.kt, stream)); }
   { Phase ph("gate", stream);
     MOBA_LAUNCH(launch_gate(in.q.data, true, in.q.st, in.q.sh, b.kbar, b.kterm, d_seqs, p, b.sel,
-                            nullptr, 0,
-                            stream)); }
+                            nullptr, 0, b.rb.gcount, stream)); }
   if (routed) {
     Phase ph("route", stream);
     MOBA_LAUNCH(launch_route(b.sel, d_seqs, p, b.rb, stream));
@@ -1327,7 +1340,8 @@ moba_status moba_select(const moba_tensor* q, const moba_tensor* k, const moba_t
   { Phase ph("gate", stream);
     MOBA_LAUNCH(launch_gate(vq.data, bf16, vq.st, vq.sh, kbar, kterm, d_seqs, p,
                             static_cast<int32_t*>(sel->data),
-                            scores ? static_cast<float*>(scores->data) : nullptr, nmax, stream)); }
+                            scores ? static_cast<float*>(scores->data) : nullptr, nmax, nullptr,
+                            stream)); }
   return MOBA_OK;
 }
 

@@ -49,6 +49,8 @@ struct Problem {
   int64_t hist_words;     // routing-histogram words per kv-head
   int64_t hist_entries;   // history selections over all rows and heads
   int tile_rows;          // query rows per attention work-group (history and causal tiles)
+  bool gate_counts;       // small batch: the gate counts its selections per block, and the
+                          // scatter scans the counts itself (route.hip)
   // the selection's layout: row (t, kv-head g, head hl of the group) of sel
   // starts at (t * sel_st + g * sel_sg + hl) * topk.  [T, Hq, topk] for the
   // callers' arrays (sel_st = Hq, sel_sg = G); kv-head-major [Hkv, T, G, topk]
@@ -67,14 +69,16 @@ hipError_t launch_pool(const void* k, bool bf16, int64_t k_st, int64_t k_sh, con
 hipError_t launch_vt_pack(const __hip_bfloat16* v, int64_t v_st, int64_t v_sh, const SeqInfo* seqs,
                           const Problem& p, __hip_bfloat16* vt, hipStream_t st);
 
-// bf16 queries read kterm (from launch_pool), fp32 queries kbar.
+// bf16 queries read kterm (from launch_pool), fp32 queries kbar.  gcount
+// (nullable): [Hkv, gate_groups, nblk_max], every group's kept past blocks.
 hipError_t launch_gate(const void* q, bool bf16, int64_t q_st, int64_t q_sh, const float* kbar,
                        const __hip_bfloat16* kterm, const SeqInfo* seqs, const Problem& p,
-                       int32_t* sel, float* scores, int nmax, hipStream_t st);
+                       int32_t* sel, float* scores, int nmax, int32_t* gcount, hipStream_t st);
 
 struct RouteBuffers {
   int32_t* hist;            // [Hkv * hist_words]: per sequence, per block a column over the
                             // sequence's chunks: counts, then exclusive offsets
+  int32_t* gcount;          // gate_counts: [Hkv, gate_groups, nblk_max] from the gate
   int32_t* bin_count;       // [Hkv * nblk_total]
   int64_t* bin_start;       // [Hkv * nblk_total + 1]
   int32_t* bin_tile_start;  // [Hkv * nblk_total + 1] tiles of tile_rows entries
@@ -87,6 +91,10 @@ struct RouteBuffers {
 inline int64_t route_tiles_bound(int64_t entries, int64_t nbins, int tile_rows) {
   return (entries + tile_rows - 1) / tile_rows + nbins;
 }
+
+// Whether a forward's or backward's batch takes the small-batch routing (p as
+// planned for the other one).
+bool route_gate_counts(const Problem& p);
 
 hipError_t launch_route(const int32_t* sel, const SeqInfo* seqs, const Problem& p,
                         const RouteBuffers& rb, hipStream_t st);

@@ -9,7 +9,8 @@
 // the GQA group).  Rows are cut into chunks of `route_rt` tokens x G heads
 // (at most kRouteRows rows) within one sequence.  Per sequence and kv-head
 // the histogram holds one column per block over the sequence's chunks.
-// Five kernels:
+// Five kernels (small batches: one, fed by counts the gate leaves, see
+// route_scatter_scan_kernel):
 //   count      per chunk: the chunk's selections, read once and coalesced
 //              (each token's G * topk entries are contiguous), counted per
 //              block in LDS and written to the blocks' columns;
@@ -381,6 +382,182 @@ __global__ __launch_bounds__(kRouteRows) void route_scatter_staged_kernel(
   }
 }
 
+// The same scatter for small batches (gate_counts), without the count and scan
+// kernels before it: those are launches of 4-5 us each that a small batch waits
+// for one after the other.  The gate has left its kept blocks counted per
+// gate group (kGroups groups per chunk); every work-group sums them over all
+// groups, one bin per thread (coalesced along the blocks), and scans the bins
+// itself, and work-group 0 writes the bin tables the attention kernels read.
+// 1033 ragged tokens, 8/2 heads, top-3: count, three scans and scatter 23 us,
+// this one 8 us (the whole forward 61 -> 49 us).
+template <int KH>
+__global__ __launch_bounds__(kRouteRows) void route_scatter_scan_kernel(
+    const int32_t* __restrict__ sel, const SeqInfo* __restrict__ seqs, Problem p,
+    const int32_t* __restrict__ gcount, int32_t* __restrict__ bin_count,
+    int64_t* __restrict__ bin_start, int32_t* __restrict__ bin_tile_start,
+    int32_t* __restrict__ tile_bin, uint32_t* __restrict__ entries) {
+  extern __shared__ uint32_t lds[];
+  __shared__ uint32_t wsum[kRouteRows / 64], wtile[kRouteRows / 64];
+  constexpr int kWords = kRouteRows / 32;
+  const int g = blockIdx.y;
+  const ChunkPos cp = chunk_pos(seqs, p, blockIdx.x);
+  const SeqInfo sq = seqs[cp.s];
+  const int nb = sq.nblk;
+  const int kh = p.topk - 1;
+  uint32_t* mask = lds;                                  // as in the staged scatter
+  uint32_t* seg = mask + kWords * nb;
+  uint32_t* ccnt = seg + nb;
+  uint32_t* base = ccnt + nb;                            // [nb] first entry of block j's run
+  uint16_t* ent = reinterpret_cast<uint16_t*>(base + nb);
+  uint16_t* pre = ent + kRouteRows * kh;
+  const int tid = threadIdx.x, word = tid >> 5, bit = tid & 31;
+  const int lane = tid & 63, wave = tid >> 6;
+
+  for (int x = tid; x < kWords * nb; x += kRouteRows) mask[x] = 0;
+  // this thread's row and its selections (requested before the counts)
+  const int nrow = cp.ntok * p.G;
+  const bool valid = tid < nrow;
+  const int tl = cp.tl0 + tid / p.G, hl = tid % p.G;
+  const int nh = valid ? min(kh, tl / p.B) : 0;
+  int js[KH];
+  const int32_t* mine =
+      sel + ((int64_t)(sq.tok_start + tl) * p.sel_st + (int64_t)g * p.sel_sg + hl) * p.topk;
+#pragma unroll
+  for (int x = 0; x < KH; x++) js[x] = x < nh ? mine[x] : -1;
+
+  // this thread's bin: its total, and for the work-group's own sequence and
+  // kv-head the entries of earlier chunks and of this one
+  const int nbins = p.Hkv * p.nblk_total;
+  const int ngrp_chunk = p.route_rt / p.gate_tw;  // gate groups per chunk
+  uint32_t total = 0, before = 0, own = 0;
+  bool ours = false;
+  int jb = 0;
+  if (tid < nbins) {
+    const int gb = tid / p.nblk_total, b = tid % p.nblk_total;
+    const int sb = find_seq(seqs, p.S, b, [](const SeqInfo& x) { return x.blk_off; });
+    const SeqInfo sqb = seqs[sb];
+    jb = b - sqb.blk_off;
+    ours = gb == g && sb == cp.s;
+    const int ng = (sqb.len + p.gate_tw - 1) / p.gate_tw;
+    const int32_t* col = gcount + ((int64_t)gb * p.gate_groups + sqb.gate_off) * p.nblk_max + jb;
+    const int r0 = cp.r * ngrp_chunk, r1 = r0 + ngrp_chunk;
+    for (int r = 0; r < ng; r += 8) {
+      uint32_t v[8];
+#pragma unroll
+      for (int e = 0; e < 8; e++) v[e] = r + e < ng ? col[(int64_t)(r + e) * p.nblk_max] : 0;
+#pragma unroll
+      for (int e = 0; e < 8; e++) {
+        total += v[e];
+        before += r + e < r0 ? v[e] : 0;
+        own += r + e >= r0 && r + e < r1 ? v[e] : 0;
+      }
+    }
+  }
+  // exclusive scans of the bins' totals and of their attention tiles
+  const uint32_t ntile = (total + p.tile_rows - 1) / p.tile_rows;
+  uint32_t inc = total, tinc = ntile;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t o = __shfl_up(inc, d, 64), q = __shfl_up(tinc, d, 64);
+    if (lane >= d) {
+      inc += o;
+      tinc += q;
+    }
+  }
+  if (lane == 63) {
+    wsum[wave] = inc;
+    wtile[wave] = tinc;
+  }
+  __syncthreads();
+  uint32_t start = inc - total, tstart = tinc - ntile;
+  for (int w = 0; w < wave; w++) {
+    start += wsum[w];
+    tstart += wtile[w];
+  }
+  if (ours) {
+    ccnt[jb] = own;
+    base[jb] = start + before;
+  }
+  if (blockIdx.x == 0 && g == 0) {
+    if (tid < nbins) {
+      bin_count[tid] = (int32_t)total;
+      bin_start[tid] = start;
+      bin_tile_start[tid] = (int32_t)tstart;
+      for (uint32_t x = 0; x < ntile; x++) tile_bin[tstart + x] = tid;
+    }
+    if (tid == nbins - 1) {
+      bin_start[nbins] = start + total;
+      bin_tile_start[nbins] = (int32_t)(tstart + ntile);
+    }
+  }
+#pragma unroll
+  for (int x = 0; x < KH; x++)
+    if (js[x] >= 0) atomicOr(&mask[word * nb + js[x]], 1u << bit);
+  __syncthreads();
+  // segment starts (wave 0) and, per block, rows of the chunk in the words
+  // below each word
+  if (wave == 0) {
+    uint32_t run = 0;
+    for (int j0 = 0; j0 < nb; j0 += 64) {
+      const int j = j0 + lane;
+      const uint32_t v = j < nb ? ccnt[j] : 0;
+      uint32_t in = v;
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t o = __shfl_up(in, d, 64);
+        if (lane >= d) in += o;
+      }
+      if (j < nb) seg[j] = run + in - v;
+      run += __shfl(in, 63, 64);
+    }
+  }
+  for (int j = tid; j < nb; j += kRouteRows) {
+    uint32_t acc = 0;
+#pragma unroll
+    for (int w = 0; w < kWords; w++) {
+      pre[w * nb + j] = (uint16_t)acc;
+      acc += __popc(mask[w * nb + j]);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int x = 0; x < KH; x++) {
+    if (js[x] >= 0) {
+      const int j = js[x];
+      const uint32_t rank = pre[word * nb + j] + __popc(mask[word * nb + j] & ((1u << bit) - 1u));
+      ent[seg[j] + rank] = (uint16_t)((tid << 5) | x);
+    }
+  }
+  __syncthreads();
+  const uint64_t r0 = (uint64_t)g * ((uint64_t)p.T * p.G) + (uint64_t)(sq.tok_start + cp.tl0) * p.G;
+  for (int j = wave; j < nb; j += kRouteRows / 64) {
+    const uint32_t n = ccnt[j];
+    uint32_t* dst = entries + base[j];
+    const uint16_t* srcj = ent + seg[j];
+    for (uint32_t e = lane; e < n; e += 64) {
+      const uint32_t code = srcj[e];
+      dst[e] = (uint32_t)((r0 + (code >> 5)) * (uint64_t)kh + (code & 31u));
+    }
+  }
+}
+
+template <int KH>
+hipError_t launch_scan_scatter(const int32_t* sel, const SeqInfo* seqs, const Problem& p,
+                               const RouteBuffers& rb, hipStream_t st) {
+  const size_t lds = staged_lds_bytes(p.nblk_max, p.topk - 1) + (size_t)p.nblk_max * 4;
+  if (lds > 65536 - 256) {
+    const hipError_t e = hipFuncSetAttribute(
+        reinterpret_cast<const void*>(&route_scatter_scan_kernel<KH>),
+        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  dim3 grid((unsigned)p.route_chunks, p.Hkv);
+  route_scatter_scan_kernel<KH><<<grid, kRouteRows, lds, st>>>(
+      sel, seqs, p, rb.gcount, rb.bin_count, rb.bin_start, rb.bin_tile_start, rb.tile_bin,
+      rb.entries);
+  return hipGetLastError();
+}
+
 template <int KH>
 hipError_t launch_staged(dim3 grid, size_t lds, const int32_t* sel, const SeqInfo* seqs,
                          const Problem& p, const RouteBuffers& rb, hipStream_t st) {
@@ -398,10 +575,33 @@ hipError_t launch_staged(dim3 grid, size_t lds, const int32_t* sel, const SeqInf
 
 }  // namespace
 
+// The small-batch scatter takes one bin per thread, up to 31 selections per
+// row, and room in LDS beside the staged entries.  Every work-group reads every count, so their product is bounded:
+// 4M words are 16 MB from L2, about the time of one of the launches saved
+// (8192 tokens, 32 heads: 256 work-groups x 16K words).  The counts lie where
+// the partials of a single kv-head fit, so no call needs more workspace.
+bool route_gate_counts(const Problem& p) {
+  const int64_t kh = p.topk - 1;
+  const int64_t nbins = (int64_t)p.Hkv * p.nblk_total;
+  const int64_t words = (int64_t)p.Hkv * p.gate_groups * p.nblk_max;
+  return kh >= 1 && kh <= 31 && nbins <= kRouteRows && p.hist_entries > 0 &&
+         p.route_chunks * p.Hkv * words <= (int64_t(4) << 20) &&
+         staged_lds_bytes(p.nblk_max, (int)kh) + (size_t)p.nblk_max * 4 + 256 <= kRouteLdsMax &&
+         words * 4 <= p.T * p.G * kh * kHeadDim * 2;
+}
+
 hipError_t launch_route(const int32_t* sel, const SeqInfo* seqs, const Problem& p,
                         const RouteBuffers& rb, hipStream_t st) {
   const int64_t nbins = (int64_t)p.Hkv * p.nblk_total;
   if (nbins == 0) return hipSuccess;
+  if (p.gate_counts) {
+    const int kh = p.topk - 1;
+    if (kh <= 3) return launch_scan_scatter<3>(sel, seqs, p, rb, st);
+    if (kh <= 7) return launch_scan_scatter<7>(sel, seqs, p, rb, st);
+    if (kh <= 11) return launch_scan_scatter<11>(sel, seqs, p, rb, st);
+    if (kh <= 15) return launch_scan_scatter<15>(sel, seqs, p, rb, st);
+    return launch_scan_scatter<31>(sel, seqs, p, rb, st);
+  }
   if (p.route_chunks > 0) {
     dim3 grid((unsigned)p.route_chunks, p.Hkv);
     route_count_kernel<<<grid, 256, p.nblk_max * sizeof(int32_t), st>>>(sel, seqs, p, rb.hist);
