@@ -48,26 +48,15 @@ enum { kHist = 0, kCur = 1 };
 constexpr int kRows = kTileRowsMfma;  // query rows per dQ work-group (256)
 constexpr float kLog2e = 1.4426950408889634f;
 
-// Per-lane DMA sources of one 64-key tile set: lane chunk p = 64j + L of DMA
-// instruction j holds row p / 17, chunk min(p % 17, 15) of a row-major tile
-// and row p / 9, chunk min(p % 9, 7) of a packed tile.
-__device__ __forceinline__ void init_dma(Dma& D, int wave, int lane, const char* base, int64_t st_bytes,
-                                         int64_t len, const char* packed) {
-  D.wave = wave;
+constexpr int kDqWaves = kRows / 32;
+
+// DMA sources of one 64-key tile set.
+__device__ __forceinline__ void init_dma(Dma<kDqWaves>& D, int wave, int lane, const char* base,
+                                         int64_t st_bytes, int64_t len, const char* packed) {
+  dma_lanes(D, wave, lane, st_bytes);
   D.kbase = base;
-  D.k_tile = kKeyTile * st_bytes;
   D.len = len;
   D.klast = base + (len - 1) * st_bytes;
-#pragma unroll
-  for (int x = 0; x < 3; x++) {
-    const int pk = 64 * (wave + 8 * x) + lane;
-    const int row = min(pk / kRowK, kKeyTile - 1), c = min(pk % kRowK, kRowK - 2);
-    D.krow[x] = row;
-    D.kcol[x] = (uint32_t)(c * 16);
-    D.koff[x] = (uint32_t)(row * st_bytes) + D.kcol[x];
-    const int vrow = min(pk / kRowV, kHeadDim - 1), vc = min(pk % kRowV, kRowV - 2);
-    D.voff[x] = (uint32_t)(vrow * (kKeyTile * 2) + vc * 16);
-  }
   D.vbase = packed;
 }
 
@@ -173,7 +162,7 @@ struct VDma {
   uint32_t st;  // token stride in bytes
 };
 
-__device__ __forceinline__ void dma_vrow(const Dma& D, const VDma& V, int i, u32x4* buf) {
+__device__ __forceinline__ void dma_vrow(const Dma<kDqWaves>& D, const VDma& V, int i, u32x4* buf) {
   const int64_t base = (int64_t)i * kKeyTile;
   const char* tile = V.base + (int64_t)i * V.tile;
   const bool tail = base + kKeyTile > D.len;
@@ -276,7 +265,7 @@ __global__ __launch_bounds__(512, 1) void bwd_dq_kernel(BwdArgs a, Problem p) {
   // ------------------------------------------------------------ key tiles
   const int64_t rb = kbeg - tok0, re = kend - tok0;
   const int i0 = (int)(rb / kKeyTile), i1 = (int)((re + kKeyTile - 1) / kKeyTile);
-  Dma DK;  // K row-major and the packed K^T
+  Dma<kDqWaves> DK;  // K row-major and the packed K^T
   VDma DV;  // V row-major
   {
     const int wv = __builtin_amdgcn_readfirstlane(wave);

@@ -52,28 +52,51 @@ __device__ __forceinline__ int64_t uniform64(int64_t v) {
   return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
+__device__ __forceinline__ const char* uniform_ptr(const char* p) {
+  return reinterpret_cast<const char*>(uniform64((int64_t)reinterpret_cast<uintptr_t>(p)));
+}
+
 __device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
-// Global sources of this thread's lane in the LDS DMA of a tile.  DMA
-// instruction j writes buffer chunks 64j .. 64j+63; wave w issues j = w + 8x
-// (x = 0..2, while j < kDmaK or kDmaV).  Lane L of instruction j fills chunk
-// p = 64j + L: K row p / 17, chunk min(p % 17, 15); V^T row p / 9, chunk
-// min(p % 9, 7).  Addresses are a wave-uniform base plus a 32-bit per-lane
-// byte offset.
+// Global sources of this thread's lane in the LDS DMA of a tile by a
+// work-group of NW waves.  DMA instruction j writes buffer chunks 64j .. 64j+63;
+// wave w issues j = w + NW x (while j < kDmaK or kDmaV).  Lane L of instruction j
+// fills chunk p = 64j + L: K row p / 17, chunk min(p % 17, 15); V^T row p / 9,
+// chunk min(p % 9, 7).  Addresses are a wave-uniform base plus a 32-bit
+// per-lane byte offset.
+template <int NW>
 struct Dma {
+  static constexpr int kX = (kDmaV + NW - 1) / NW;  // instructions per wave, at most
   const char* kbase;  // K of this kv-head at the sequence start (uniform)
   int64_t k_tile;     // bytes between consecutive key tiles (uniform)
   int64_t len;        // sequence length
   const char* klast;  // the sequence's last key row (uniform)
-  uint32_t koff[3];   // per-lane byte offset of the chunk within a tile
-  uint32_t kcol[3];   // per-lane byte offset of the chunk within its row
-  int krow[3];        // tile row of the lane's chunk
+  uint32_t koff[kX];  // per-lane byte offset of the chunk within a tile
+  uint32_t kcol[kX];  // per-lane byte offset of the chunk within its row
+  int krow[kX];       // tile row of the lane's chunk
   const char* vbase;  // packed V^T tile 0 (uniform)
-  uint32_t voff[3];
+  uint32_t voff[kX];
   int wave;           // wave-uniform
 };
+
+// The per-lane part.
+template <int NW>
+__device__ __forceinline__ void dma_lanes(Dma<NW>& D, int wave, int lane, int64_t st_bytes) {
+  D.wave = wave;
+  D.k_tile = kKeyTile * st_bytes;
+#pragma unroll
+  for (int x = 0; x < Dma<NW>::kX; x++) {
+    const int pk = 64 * (wave + NW * x) + lane;
+    const int row = min(pk / kRowK, kKeyTile - 1), c = min(pk % kRowK, kRowK - 2);
+    D.krow[x] = row;
+    D.kcol[x] = (uint32_t)(c * 16);
+    D.koff[x] = (uint32_t)(row * st_bytes) + D.kcol[x];
+    const int vrow = min(pk / kRowV, kHeadDim - 1), vc = min(pk % kRowV, kRowV - 2);
+    D.voff[x] = (uint32_t)(vrow * (kKeyTile * 2) + vc * 16);
+  }
+}
 
 // One LDS DMA instruction: 16 bytes per lane from global memory into LDS,
 // lane L to 16-byte chunk L of the 1 KiB at ldst (global_load_lds_dwordx4,
@@ -101,38 +124,39 @@ __device__ __forceinline__ void dma16_at(const char* base, uint32_t off, u32x4* 
                : : "v"(off), "s"(base), "{m0}"(lds_addr(ldst)) : "memory");
 }
 
-__device__ __forceinline__ void dma_k1(const Dma& D, const char* tile, bool tail, int64_t base,
+template <int NW>
+__device__ __forceinline__ void dma_k1(const Dma<NW>& D, const char* tile, bool tail, int64_t base,
                                        u32x4* buf, int x) {
   uint32_t off = D.koff[x];
   // rows past the sequence end repeat its last key; they are always masked
   // (the tile starts at or before the last key, so the offset stays >= 0)
   if (tail && base + D.krow[x] >= D.len) off = (uint32_t)(D.klast - tile) + D.kcol[x];
-  dma16_at(tile, off, buf + 64 * (D.wave + 8 * x));
+  dma16_at(tile, off, buf + 64 * (D.wave + NW * x));
 }
 
-__device__ __forceinline__ void dma_k(const Dma& D, int i, u32x4* buf) {
+template <int NW>
+__device__ __forceinline__ void dma_k(const Dma<NW>& D, int i, u32x4* buf) {
   const int64_t base = (int64_t)i * kKeyTile;
   const char* tile = D.kbase + (int64_t)i * D.k_tile;
-  if (base + kKeyTile <= D.len) {
-    dma_k1(D, tile, false, base, buf, 0);
-    dma_k1(D, tile, false, base, buf, 1);
-    if (D.wave + 16 < kDmaK) dma_k1(D, tile, false, base, buf, 2);
+  const bool tail = base + kKeyTile > D.len;
+  if (!tail) {
+#pragma unroll
+    for (int x = 0; x < Dma<NW>::kX; x++)
+      if (NW * (x + 1) <= kDmaK || D.wave + NW * x < kDmaK) dma_k1(D, tile, false, base, buf, x);
   } else {
-    dma_k1(D, tile, true, base, buf, 0);
-    dma_k1(D, tile, true, base, buf, 1);
-    if (D.wave + 16 < kDmaK) dma_k1(D, tile, true, base, buf, 2);
+#pragma unroll
+    for (int x = 0; x < Dma<NW>::kX; x++)
+      if (NW * (x + 1) <= kDmaK || D.wave + NW * x < kDmaK) dma_k1(D, tile, true, base, buf, x);
   }
 }
 
-__device__ __forceinline__ void dma_v1(const Dma& D, const char* tile, u32x4* buf, int x) {
-  dma16_at(tile, D.voff[x], buf + 64 * (D.wave + 8 * x));
-}
-
-__device__ __forceinline__ void dma_v(const Dma& D, int i, u32x4* buf) {
+template <int NW>
+__device__ __forceinline__ void dma_v(const Dma<NW>& D, int i, u32x4* buf) {
   const char* tile = D.vbase + (int64_t)i * (kChunksV * 16);
-  dma_v1(D, tile, buf, 0);
-  dma_v1(D, tile, buf, 1);
-  if (D.wave + 16 < kDmaV) dma_v1(D, tile, buf, 2);
+#pragma unroll
+  for (int x = 0; x < Dma<NW>::kX; x++)
+    if (NW * (x + 1) <= kDmaV || D.wave + NW * x < kDmaV)
+      dma16_at(tile, D.voff[x], buf + 64 * (D.wave + NW * x));
 }
 
 // Wait for this wave's LDS DMA (and everything else) before a barrier.

@@ -5,8 +5,8 @@
 // moba_forward enqueues, on the caller's stream:
 //   pool -> [bf16: V^T pack] -> gate -> route (count, column scan, bin scan,
 //   scatter) -> per chunk of kv-heads: history attention, then current-block
-//   attention (fp32: both in one launch), then the merge of the history
-//   partials, in place on the output.
+//   attention (fp32 and short blocks: both in one launch), then the merge of
+//   the history partials, in place on the output.
 // Only the attention steps depend on the chunk; their workspace (the
 // partials: bf16 on the bf16 path, fp32 on the fp32 path) is what the
 // workspace cap limits.
@@ -789,16 +789,17 @@ moba_status moba_forward(const moba_tensor* q, const moba_tensor* k, const moba_
         kh > 0 && e_chunk > 0
             ? ceil_div(e_chunk, p.tile_rows) + (int64_t)(a.g1 - a.g0) * p.nblk_total
             : 0;
-    if (in.bf16) {
+    if (!in.bf16 || attn_bf16_joint(p)) {
+      Phase ph("attn_hist", stream);  // and the current-block tiles
+      MOBA_LAUNCH(in.bf16 ? launch_attn_joint_bf16(a, p, hist_tiles, stream)
+                          : launch_attn_f32(a, p, hist_tiles, stream));
+    } else {
       if (hist_tiles > 0) {
         Phase ph("attn_hist", stream);
         MOBA_LAUNCH(launch_attn_hist_bf16(a, p, hist_tiles, stream));
       }
       Phase ph("attn_cur", stream);
       MOBA_LAUNCH(launch_attn_causal_bf16(false, a, p, stream));
-    } else {
-      Phase ph("attn_hist", stream);  // and the current-block tiles
-      MOBA_LAUNCH(launch_attn_f32(a, p, hist_tiles, stream));
     }
     if (kh > 0) {
       Phase ph("merge", stream);

@@ -128,6 +128,10 @@ struct AttnArgs {
 // (extra work-groups exit).  Causal tiles: a.ntiles x (g1 - g0) work-groups.
 hipError_t launch_attn_hist_bf16(const AttnArgs& a, const Problem& p, int64_t grid, hipStream_t st);
 hipError_t launch_attn_causal_bf16(bool dense, const AttnArgs& a, const Problem& p, hipStream_t st);
+// bf16, where attn_bf16_joint(p): history and causal tiles in one launch.
+bool attn_bf16_joint(const Problem& p);
+hipError_t launch_attn_joint_bf16(const AttnArgs& a, const Problem& p, int64_t hist_tiles,
+                                  hipStream_t st);
 // fp32: the chunk's history tiles (at most hist_tiles, 0: none) and its causal
 // tiles in one launch.
 hipError_t launch_attn_f32(const AttnArgs& a, const Problem& p, int64_t hist_tiles, hipStream_t st);

@@ -1,0 +1,32 @@
+"""History and current-block tiles in one launch of 128-row work-groups (blocks of
+up to 2048 keys): tile remainders, groups whose 256-row plan tile splits unevenly,
+waves without a key in a causal tile's last key tiles, no history at all."""
+import pytest
+import torch
+
+from paper_2502_13189_amd import inputs
+import parity
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+@pytest.mark.parametrize("seqlens,hq,hkv,B,topk", [
+    ((127, 129, 257), 1, 1, 64, 2),     # MHA row counts around 128 and 256
+    ((700,), 3, 1, 300, 2),             # groups of 3: 85 tokens (255 rows) per plan tile
+    ((190,), 100, 1, 50, 2),            # 2 tokens (200 rows): the second half holds 72
+    ((600, 1), 2, 2, 2, 3),             # two-key blocks: many bins of few rows
+    ((900,), 2, 1, 256, 1),             # top-1: causal tiles only
+    ((4300,), 1, 1, 2048, 2),           # the longest blocks of the joint launch
+    ((4200,), 1, 1, 2049, 2),           # and the first beyond it
+])
+def test_joint_tiles(seqlens, hq, hkv, B, topk):
+    q, k, v, cu = inputs.make(seqlens, hq, hkv, 128, torch.bfloat16, B, 0.5, B, device=DEV)
+    r = parity.moba_parity(q, k, v, cu, B, topk, dtype="bf16")
+    print("max_abs %.2e lse %.2e" % (r["max_abs"], r["lse_max_abs"]))
