@@ -358,7 +358,7 @@ __global__ __launch_bounds__(512, 1) void bwd_dq_kernel(BwdArgs a, Problem p) {
       for (int r = 0; r < 16; r++) acc[dt][r] *= scl;
     // history slots of this row, in slot order
     const int kh = p.topk - 1;
-    const int nh = (int)min((int64_t)kh, (r.t - tok0) / p.B);
+    const int nh = routed_slots(sq, p, (int)(r.t - tok0) / p.B);
     const float* part = a.dq_part + r.dst * kh * kHeadDim;
     for (int x = 0; x < nh; x++) {
 #pragma unroll
@@ -735,7 +735,14 @@ __global__ __launch_bounds__(64 * kDkdvWaves, 1) void bwd_dkdv_kernel(BwdArgs a,
       const char* qr = reinterpret_cast<const char*>(lds + (i % 3) * kBufR);
       const char* dr = reinterpret_cast<const char*>(lds + (3 + cur) * kBufR);
       const int slot = i % kSlots;
-      const bool edge = (int64_t)(i + 1) * kChunk > L.nhist || !full;
+      // masks are needed where rows are missing (list end, partial key tile) or
+      // may precede a key: the first kKeysPerDkdv unrouted rows of each head
+      bool edge = (int64_t)(i + 1) * kChunk > L.nhist || !full;
+      if (edge && full) {
+        const int64_t x0 = (int64_t)i * kChunk - L.nhist;
+        const int off = x0 >= 0 ? (int)x0 % L.nct : 0;
+        edge = off < kKeysPerDkdv || off + kChunk > L.nct || x0 + L.nhist + kChunk > L.nrows;
+      }
 #pragma unroll 1
       for (int st = 0; st < 2; st++) {
         if (!live) continue;

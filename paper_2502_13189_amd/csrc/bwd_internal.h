@@ -9,8 +9,9 @@ namespace moba {
 constexpr int kDkdvWaves = 8;                       // waves per dK/dV work-group (two per SIMD)
 constexpr int kKeysPerDkdv = 32 * (kDkdvWaves / 2);  // keys per dK/dV work-group (32 per SIMD)
 
-// Keys [k0, k1) of global block b; the block's tokens end at bend.  One dK/dV
-// work-group per key tile and kv-head.
+// Keys [k0, k1) of global block b; the rows of tokens [k0, bend) attend them
+// without routing (the block's own rows; in a head block, those of the whole
+// head).  One dK/dV work-group per key tile and kv-head.
 struct KeyTile {
   int32_t b;
   int32_t k0;

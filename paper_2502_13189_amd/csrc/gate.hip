@@ -100,11 +100,11 @@ __device__ __forceinline__ void write_sel(int32_t* out, const int* id, int c, in
 // Every thread of the work-group calls it.
 template <int KM>
 __device__ __forceinline__ void count_kept(int32_t* cnt, int nb, bool valid, const int* id, int c,
-                                           int K, int32_t* dst) {
+                                           int K, int head, int32_t* dst) {
   __syncthreads();
   for (int j = threadIdx.x; j < nb; j += 256) cnt[j] = 0;
   __syncthreads();
-  if (valid) {
+  if (valid && c >= head) {
     if (KM > 0 && c >= K) {
 #pragma unroll
       for (int x = 0; x < KM; x++)
@@ -158,7 +158,8 @@ __global__ __launch_bounds__(256) void gate_kernel(const T* __restrict__ q, int6
       id[x] = 0x7fffffff;
     }
   }
-  const bool need_scores = KM > 0 || scores != nullptr;
+  // (no row of a group within the head blocks is routed, so none needs its list)
+  const bool need_scores = (KM > 0 && (sq.head <= 1 || cmax >= sq.head)) || scores != nullptr;
   if (need_scores && cmax > 0) {
     float qf[kHeadDim];
     if (valid) load_q<T>(q + t * q_st + (int64_t)hl * q_sh + (int64_t)g * p.G * q_sh, qf);
@@ -194,9 +195,9 @@ __global__ __launch_bounds__(256) void gate_kernel(const T* __restrict__ q, int6
     }
   }
   if (gcount)
-    count_kept<KM>(reinterpret_cast<int32_t*>(kb), sq.nblk, valid, id, c, K,
+    count_kept<KM>(reinterpret_cast<int32_t*>(kb), sq.nblk, valid, id, c, K, sq.head,
                    gcount + ((int64_t)g * p.gate_groups + blockIdx.x) * p.nblk_max);
-  if (!valid) return;
+  if (!valid || (sq.head > 1 && c < sq.head)) return;
   write_sel<KM>(sel + srow * K, id, c, K);
 }
 
@@ -294,7 +295,8 @@ void gate_mfma_kernel(const __hip_bfloat16* __restrict__ q, int64_t q_st, int64_
       li[x] = 0x7fffffff;
     }
   }
-  const bool need_scores = KM > 0 || scores != nullptr;
+  // (no row of a group within the head blocks is routed, so none needs its list)
+  const bool need_scores = (KM > 0 && (sq.head <= 1 || cmax >= sq.head)) || scores != nullptr;
   if (need_scores && cmax > 0) {
     // Q^T operands of the two 32-row sets of this wave: lane (qc, hh) holds
     // dims 16 kk + 8 hh .. + 7 of row 64 wave + 32 set + qc.
@@ -450,9 +452,9 @@ void gate_mfma_kernel(const __hip_bfloat16* __restrict__ q, int64_t q_st, int64_
     }
   }
   if (gcount)
-    count_kept<KM>(reinterpret_cast<int32_t*>(terms), sq.nblk, valid, li, c, K,
+    count_kept<KM>(reinterpret_cast<int32_t*>(terms), sq.nblk, valid, li, c, K, sq.head,
                    gcount + ((int64_t)g * p.gate_groups + blockIdx.x) * p.nblk_max);
-  if (!valid) return;
+  if (!valid || (sq.head > 1 && c < sq.head)) return;
   write_sel<KM>(sel + srow * K, li, c, K);
 }
 

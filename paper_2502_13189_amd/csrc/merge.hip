@@ -71,9 +71,10 @@ __global__ __launch_bounds__(256) void merge_kernel(AttnArgs a, Problem p) {
   const int64_t t = rem / p.G;
   const int h = (a.g0 + gl) * p.G + (int)(rem % p.G);
   const int s = find_seq(a.seqs, p.S, t, [](const SeqInfo& x) { return x.tok_start; });
-  const int64_t c = (t - a.seqs[s].tok_start) / p.B;
+  const SeqInfo sq = a.seqs[s];
+  const int c = ((int)t - sq.tok_start) / p.B;
   const int kh = p.topk - 1;
-  const int nh = (int)min((int64_t)kh, c);
+  const int nh = routed_slots(sq, p, c);
   if (nh <= 0) return;
 
   uint4* orow = reinterpret_cast<uint4*>(static_cast<T*>(a.out) + t * a.o_st + (int64_t)h * a.o_sh +

@@ -215,10 +215,26 @@ struct Plan {
   std::vector<SeqInfo> seqs;
   std::vector<CausalTile> tiles;
   std::vector<KeyTile> ktiles;  // key tiles of the dK/dV kernel (kTilesCur plans)
-  int64_t hist_per_head = 0;  // history selections of one query head, summed over tokens
+  int64_t hist_per_head = 0;  // routed history selections of one query head, summed over tokens
 };
 
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+// Rows of a sequence's first topk blocks keep every past block, i.e. attend
+// their whole prefix: a causal tile then does what routed tiles, their partials
+// and the merge would, and the gate has nothing to choose.  But such a tile is
+// up to topk blocks long, so only where the sequence's causal tiles alone keep
+// half of the chip's 512 128-row work-groups busy for that long.  (Of the
+// sequence alone, so that its rows do not depend on the batch.)  The whole
+// forward, all rows routed, then with the head: 8192 tokens, 32 heads, B = 512,
+// top-3: 366 -> 352 us; 32K tokens, B = 256, top-32: 8.64 -> 7.97 ms; 112K ragged
+// tokens, B = 1024, top-4: 8.93 -> 8.76 ms.
+int head_blocks(int64_t L, int G, int Hkv, int B, int topk) {
+  if (B < 1 || topk < 2) return 1;
+  const double h = (double)std::min<int64_t>(L, (int64_t)topk * B);
+  const double pairs = 0.5 * h * h + 0.5 * B * (L - h);
+  return pairs * G * Hkv / 128 >= 256.0 * h ? topk : 1;
+}
 
 // B = 0 means "one block per sequence" (dense attention).
 void build_plan(const std::vector<int32_t>& cu, int Hq, int Hkv, int B, int topk, TileMode mode,
@@ -238,7 +254,7 @@ void build_plan(const std::vector<int32_t>& cu, int Hq, int Hkv, int B, int topk
   p.sel_st = Hq;  // the callers' [T, Hq, topk]
   p.sel_sg = p.G;
   pl->seqs.assign(S, SeqInfo{});
-  int64_t blk = 0, vt = 0, gate = 0, rc = 0, hw = 0, hist = 0;
+  int64_t blk = 0, vt = 0, gate = 0, rc = 0, hw = 0, hist = 0, all = 0;
   int nbmax = 0;
   const int64_t kh = topk - 1;
   for (int s = 0; s < S; s++) {
@@ -254,6 +270,7 @@ void build_plan(const std::vector<int32_t>& cu, int Hq, int Hkv, int B, int topk
     q.gate_off = (int32_t)gate;
     q.rc_off = (int32_t)rc;
     q.hist_off = hw;
+    q.head = mode == kTilesCur ? head_blocks(L, p.G, Hkv, B, topk) : 1;
     blk += nb;
     vt += ceil_div(L, kKeyTile);
     gate += ceil_div(L, p.gate_tw);
@@ -263,7 +280,8 @@ void build_plan(const std::vector<int32_t>& cu, int Hq, int Hkv, int B, int topk
     if (B > 0)
       for (int64_t c = 0; c < nb; c++) {
         const int64_t m = std::min<int64_t>(L, (c + 1) * B) - c * B;
-        hist += m * std::min<int64_t>(kh, c);
+        all += m * std::min<int64_t>(kh, c);
+        if (c >= q.head) hist += m * std::min<int64_t>(kh, c);
       }
   }
   p.nblk_total = (int)blk;
@@ -274,6 +292,7 @@ void build_plan(const std::vector<int32_t>& cu, int Hq, int Hkv, int B, int topk
   p.hist_words = hw;
   pl->hist_per_head = hist;
   p.hist_entries = hist * Hq;
+  p.all_entries = all * Hq;
   if (mode == kTilesCur && route_gate_counts(p)) {
     // routing chunks of whole gate groups (hist_words keeps the workspace's size)
     p.gate_counts = true;
@@ -293,22 +312,31 @@ void build_plan(const std::vector<int32_t>& cu, int Hq, int Hkv, int B, int topk
   if (mode == kTilesCur) {
     // Tiles of one key block read the same K/V.  Work-groups go round-robin
     // to the 8 XCDs (each with its own L2), so each block's tiles are put on
-    // one XCD, longest first, with blocks spread greedily over the XCDs by
-    // key work; tile x of the list runs on XCD x % 8 (the list is padded
-    // with empty tiles to a multiple of 8).
-    struct Group { int64_t work; std::vector<CausalTile> tiles; };
+    // one XCD, with blocks (and single head tiles, which are too much for one
+    // XCD together) spread greedily over the XCDs by key work; each XCD then
+    // takes the groups with the longest tiles first, a group's longest tile
+    // first.  Tile x of the list runs on XCD x % 8 (the list is padded with
+    // empty tiles to a multiple of 8).
+    struct Group { int64_t work, longest; std::vector<CausalTile> tiles; };
     std::vector<Group> groups;
     for (int s = 0; s < S; s++) {
       const int64_t L = (int64_t)cu[s + 1] - cu[s];
-      for (int64_t b0 = 0; b0 < L; b0 += B) {
-        const int64_t b1 = std::min(L, b0 + B);
-        Group gr{0, {}};
+      const int head = pl->seqs[s].head;
+      for (int64_t b0 = 0, b1; b0 < L; b0 = b1) {
+        b1 = std::min(L, b0 + (b0 == 0 ? (int64_t)head * B : B));
+        Group gr{0, 0, {}};
         for (int64_t t0 = b0; t0 < b1; t0 += tt) {
           const int64_t t1 = std::min(b1, t0 + tt);
           gr.tiles.push_back(CausalTile{s, (int32_t)(cu[s] + t0), (int32_t)(cu[s] + t1),
                                         (int32_t)(cu[s] + b0)});
           gr.work += t1 - b0;
+          gr.longest = t1 - b0;
+          if (b0 == 0 && head > 1) {
+            groups.push_back(std::move(gr));
+            gr = Group{0, 0, {}};
+          }
         }
+        if (gr.tiles.empty()) continue;
         std::reverse(gr.tiles.begin(), gr.tiles.end());
         groups.push_back(std::move(gr));
       }
@@ -316,18 +344,25 @@ void build_plan(const std::vector<int32_t>& cu, int Hq, int Hkv, int B, int topk
     std::stable_sort(groups.begin(), groups.end(),
                      [](const Group& x, const Group& y) { return x.work > y.work; });
     constexpr int kXcd = 8;
-    std::vector<std::vector<CausalTile>> lists(kXcd);
+    std::vector<std::vector<const Group*>> lists(kXcd);
     int64_t load[kXcd] = {0};
     for (const Group& gr : groups) {
       const int x = (int)(std::min_element(load, load + kXcd) - load);
-      lists[x].insert(lists[x].end(), gr.tiles.begin(), gr.tiles.end());
+      lists[x].push_back(&gr);
       load[x] += gr.work;
     }
+    std::vector<std::vector<CausalTile>> order(kXcd);
     size_t n = 0;
-    for (const auto& l : lists) n = std::max(n, l.size());
+    for (int x = 0; x < kXcd; x++) {
+      std::stable_sort(lists[x].begin(), lists[x].end(),
+                       [](const Group* a, const Group* b) { return a->longest > b->longest; });
+      for (const Group* gr : lists[x])
+        order[x].insert(order[x].end(), gr->tiles.begin(), gr->tiles.end());
+      n = std::max(n, order[x].size());
+    }
     for (size_t k = 0; k < n; k++)
       for (int x = 0; x < kXcd; x++)
-        pl->tiles.push_back(k < lists[x].size() ? lists[x][k] : CausalTile{0, 0, 0, 0});
+        pl->tiles.push_back(k < order[x].size() ? order[x][k] : CausalTile{0, 0, 0, 0});
     // dK/dV key tiles: local block 0 of every sequence first (early blocks
     // collect the longest routed row lists), then block 1, ...
     for (int j = 0; j < nbmax; j++)
@@ -336,10 +371,14 @@ void build_plan(const std::vector<int32_t>& cu, int Hq, int Hkv, int B, int topk
         const int64_t b0 = (int64_t)j * B;
         if (b0 >= L) continue;
         const int64_t b1 = std::min(L, b0 + B);
+        // unrouted rows from k0 on: the block's own, in a head block the head's
+        const int64_t e1 = j < pl->seqs[s].head
+                               ? std::min<int64_t>(L, (int64_t)pl->seqs[s].head * B)
+                               : b1;
         for (int64_t k0 = b0; k0 < b1; k0 += kKeysPerDkdv)
           pl->ktiles.push_back(KeyTile{pl->seqs[s].blk_off + j, (int32_t)(cu[s] + k0),
                                        (int32_t)(cu[s] + std::min(b1, k0 + kKeysPerDkdv)),
-                                       (int32_t)(cu[s] + b1)});
+                                       (int32_t)(cu[s] + e1)});
       }
     return;
   }
@@ -658,8 +697,8 @@ void forward_layout(const Problem& p, bool bf16, int kk, int nch, Bump* bp, FwdB
   b->rb.bin_count = bp->take<int32_t>(nbins);
   b->rb.bin_start = bp->take<int64_t>(nbins + 1);
   b->rb.bin_tile_start = bp->take<int32_t>(nbins + 1);
-  b->rb.entries = bp->take<uint32_t>(p.hist_entries);
-  b->rb.tile_bin = bp->take<int32_t>(route_tiles_bound(p.hist_entries, nbins, p.tile_rows));
+  b->rb.entries = bp->take<uint32_t>(p.all_entries);
+  b->rb.tile_bin = bp->take<int32_t>(route_tiles_bound(p.all_entries, nbins, p.tile_rows));
   const int64_t rows = (int64_t)nch * p.T * p.G;
   b->o_part = bf16 ? (void*)bp->take<__hip_bfloat16>(rows * kh * kHeadDim)
                    : (void*)bp->take<float>(rows * kh * kHeadDim);
@@ -894,10 +933,10 @@ moba_status backward_impl(const moba_tensor* q, const moba_tensor* k, const moba
     b->rb.bin_count = bp->take<int32_t>(nbins);
     b->rb.bin_start = bp->take<int64_t>(nbins + 1);
     b->rb.bin_tile_start = bp->take<int32_t>(nbins + 1);
-    b->rb.entries = bp->take<uint32_t>(p.hist_entries);
-    b->rb.tile_bin = bp->take<int32_t>(route_tiles_bound(p.hist_entries, nbins, kTileRowsMfma));
+    b->rb.entries = bp->take<uint32_t>(p.all_entries);
+    b->rb.tile_bin = bp->take<int32_t>(route_tiles_bound(p.all_entries, nbins, kTileRowsMfma));
     b->ld = bp->take<float2>(p.T * p.Hq);
-    b->rec = bp->take<int4>(routed ? p.hist_entries : 0);
+    b->rec = bp->take<int4>(routed ? p.all_entries : 0);
     b->dq_part = bp->take<float>(routed ? (int64_t)nch * TG * kh * kHeadDim : 0);
     // the gate's counts are done with before the first dQ partial is written
     b->rb.gcount = p.gate_counts ? reinterpret_cast<int32_t*>(b->dq_part) : nullptr;
@@ -1434,7 +1473,7 @@ size_t moba_workspace_bytes(int64_t T, int32_t Hq, int32_t Hkv, int32_t D, int64
   p.tile_rows = std::min(kTileRowsMfma, kTileRowsF32);  // the smaller gives more tiles
   const int kk = (int)std::min<int64_t>(topk, nblk_total);
   p.hist_words = (ceil_div(T, std::max(1, kRouteRows / p.G)) + 1) * nblk_total;
-  p.hist_entries = T * Hq * (int64_t)(kk - 1);
+  p.all_entries = T * Hq * (int64_t)(kk - 1);
   size_t need = 0;
   for (int bf16 = 0; bf16 < 2; bf16++) {
     Bump bp(nullptr);

@@ -24,7 +24,10 @@ struct SeqInfo {
   int32_t vt_tile_off; // first 64-key tile of the sequence in the packed V^T layout
   int32_t gate_off;    // first gate work-group of the sequence
   int32_t rc_off;      // first routing chunk of the sequence (per kv-head)
-  int32_t pad0;
+  // rows of the sequence's first `head` blocks attend their whole prefix in one
+  // causal tile and are not routed: 1 (block 0 alone, which has no past), or
+  // topk, where the gate keeps every past block
+  int32_t head;
   int64_t hist_off;    // first routing-histogram word of the sequence (per kv-head)
 };
 
@@ -47,7 +50,8 @@ struct Problem {
   int64_t route_chunks;   // routing chunks per kv-head
   int route_rt;           // tokens per routing chunk
   int64_t hist_words;     // routing-histogram words per kv-head
-  int64_t hist_entries;   // history selections over all rows and heads
+  int64_t hist_entries;   // routed history selections over all rows and heads
+  int64_t all_entries;    // with those of unrouted rows (what the workspace is sized for)
   int tile_rows;          // query rows per attention work-group (history and causal tiles)
   bool gate_counts;       // small batch: the gate counts its selections per block, and the
                           // scatter scans the counts itself (route.hip)
@@ -139,6 +143,11 @@ hipError_t launch_attn_f32(const AttnArgs& a, const Problem& p, int64_t hist_til
 hipError_t launch_merge(bool bf16, const AttnArgs& a, const Problem& p, hipStream_t st);
 
 // ------------------------------------------------------------ device helpers
+// Routed history slots of a row of sequence sq at current block c.
+__device__ __forceinline__ int routed_slots(const SeqInfo& sq, const Problem& p, int c) {
+  return c < sq.head ? 0 : min(p.topk - 1, c);
+}
+
 // Largest s with key[s] <= x among sequences, skipping empty ones that share
 // the same start.  `field` selects the per-sequence prefix being searched.
 template <typename F>

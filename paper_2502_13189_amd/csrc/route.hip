@@ -85,7 +85,7 @@ __global__ __launch_bounds__(256) void route_count_kernel(const int32_t* __restr
     if (tk0 < tpb) {
       for (int tk = tk0; tk < cp.ntok; tk += tpb) {
         const int c = (cp.tl0 + tk) / p.B;
-        if (x < min(kh, c)) {
+        if (x < routed_slots(sq, p, c)) {
           const int j = base[tk * tok_stride + w];
           if ((unsigned)j < (unsigned)c) atomicAdd(&cnt[j], 1);
         }
@@ -97,7 +97,7 @@ __global__ __launch_bounds__(256) void route_count_kernel(const int32_t* __restr
       const int tk = e / per_tok, w = e - tk * per_tok;
       const int x = w % p.topk;
       const int c = (cp.tl0 + tk) / p.B;
-      if (x < min(kh, c)) {
+      if (x < routed_slots(sq, p, c)) {
         const int j = base[tk * tok_stride + w];
         if ((unsigned)j < (unsigned)c) atomicAdd(&cnt[j], 1);
       }
@@ -223,7 +223,7 @@ __global__ __launch_bounds__(256) void route_scatter_kernel(const int32_t* __res
     if (valid) {
       tl = cp.tl0 + i / p.G;
       hl = i % p.G;
-      nh = min(kh, tl / p.B);
+      nh = routed_slots(sq, p, tl / p.B);
       row = ((int64_t)sq.tok_start + tl) * p.sel_st + (int64_t)g * p.sel_sg + hl;
       for (int x = 0; x < nh; x++) {
         const int j = sel[row * p.topk + x];
@@ -314,7 +314,7 @@ __global__ __launch_bounds__(kRouteRows) void route_scatter_staged_kernel(
   const int nrow = cp.ntok * p.G;
   const bool valid = tid < nrow;
   const int tl = cp.tl0 + tid / p.G, hl = tid % p.G;
-  const int nh = valid ? min(kh, tl / p.B) : 0;
+  const int nh = valid ? routed_slots(sq, p, tl / p.B) : 0;
   // slots with a block outside [0, c) are skipped (-1), as by the count kernel
   int js[KH];
   const int32_t* mine =
@@ -418,7 +418,7 @@ __global__ __launch_bounds__(kRouteRows) void route_scatter_scan_kernel(
   const int nrow = cp.ntok * p.G;
   const bool valid = tid < nrow;
   const int tl = cp.tl0 + tid / p.G, hl = tid % p.G;
-  const int nh = valid ? min(kh, tl / p.B) : 0;
+  const int nh = valid ? routed_slots(sq, p, tl / p.B) : 0;
   int js[KH];
   const int32_t* mine =
       sel + ((int64_t)(sq.tok_start + tl) * p.sel_st + (int64_t)g * p.sel_sg + hl) * p.topk;
