@@ -92,6 +92,20 @@ def attended_keys(seqlens, B, topk):
     return cur, hist, sel
 
 
+def launch_keys(seqlens, B, topk, hq):
+    """(causal, routed) keys per query head: attended_keys() split as the
+    kernels take them.  Rows of a sequence's first topk blocks attend their
+    whole prefix in the causal tiles where the sequence is large enough
+    (head_blocks in moba_api.hip)."""
+    cur, hist, _ = attended_keys(seqlens, B, topk)
+    head = 0
+    for L in seqlens:
+        h = min(L, topk * B)
+        if topk >= 2 and h > 0 and (0.5 * h * h + 0.5 * B * (L - h)) * hq / 128 >= 256.0 * h:
+            head += attended_keys([h], B, topk)[1]
+    return cur + head, hist - head
+
+
 def dense_keys(seqlens):
     return sum(L * (L + 1) // 2 for L in seqlens)
 
@@ -330,6 +344,7 @@ def run_backward(args):
     binding.profile_enable(False)
     phases = binding.profile_read()
     cur, hist, _ = attended_keys(w.seqlens, w.block_size, w.topk)
+    causal, routed = launch_keys(w.seqlens, w.block_size, w.topk, w.hq)
     pairs = w.hq * (cur + hist)
     flop = 10.0 * w.d * pairs
     tflops = flop / (ms * 1e-3) / 1e12
@@ -339,12 +354,12 @@ def run_backward(args):
         n, t = phases.get(name, (0, 0.0))
         return None if not n else round(kflop / (t / args.steps * 1e-3) / 1e12, 2)
 
-    # executed products per kernel: dq history 3 (S, dP, dQ) over history
-    # pairs; dq current 3 over current-block pairs; dkdv 4 (S, dP, dV, dK)
+    # executed products per kernel: dq history 3 (S, dP, dQ) over routed
+    # pairs; dq current 3 over the causal tiles' pairs; dkdv 4 (S, dP, dV, dK)
     # over all pairs
     rates = {
-        "bwd_dq_hist": kernel_rate("bwd_dq_hist", 6.0 * w.d * w.hq * hist),
-        "bwd_dq_cur": kernel_rate("bwd_dq_cur", 6.0 * w.d * w.hq * cur),
+        "bwd_dq_hist": kernel_rate("bwd_dq_hist", 6.0 * w.d * w.hq * routed),
+        "bwd_dq_cur": kernel_rate("bwd_dq_cur", 6.0 * w.d * w.hq * causal),
         "bwd_dkdv": kernel_rate("bwd_dkdv", 8.0 * w.d * pairs),
     }
     cpu = None
@@ -492,8 +507,9 @@ def main():
     cur, hist, nsel = attended_keys(w.seqlens, w.block_size, w.topk)
     flop = 4.0 * w.d * w.hq * (cur + hist)
     tflops = flop / (ms * 1e-3) / 1e12
-    # calls without an "attn_cur" phase run their current-block tiles in the same launch
-    hist_flop_step = 4.0 * w.d * w.hq * (hist if "attn_cur" in phases else hist + cur)
+    causal, routed = launch_keys(w.seqlens, w.block_size, w.topk, w.hq)
+    # calls without an "attn_cur" phase run their causal tiles in the same launch
+    hist_flop_step = 4.0 * w.d * w.hq * (routed if "attn_cur" in phases else routed + causal)
     hl, hms = phases.get("attn_hist", (0, 0.0))
     launches_per_step = hl / max(args.steps, 1)
     achieved = (hist_flop_step / launches_per_step) / (hms / hl * 1e-3) / 1e12 if hl else 0.0
