@@ -7,15 +7,15 @@
 //
 // Decode reads each attended key once per kv-head and does ~2 FLOP per byte,
 // far below the ridge of either the matrix cores or the vector ALUs, so it is
-// bound by HBM: the kernels use the vector ALUs (packed bf16 dot products,
-// which halve the instruction count of fp32 FMAs on unpacked operands), read
-// K rows one per lane and V rows coalesced, and in MoBA mode touch only the
-// selected blocks.
+// bound by HBM and the loads decide: a probe of the bare loads ran at 4.6-5.0
+// TB/s with one key row per lane and at 5.8-6.1 TB/s with K as matrix operands (16
+// rows x 64 bytes per load) and V one row per load, the layouts used here; so S
+// comes from the matrix cores, P V from packed bf16 dot products.  In MoBA
+// mode only the selected blocks are touched.
 //
 //   gate     one work-group per (sequence, query head): fp32 scores of the
 //            query against the block means of the sequence's complete past
-//            blocks (coalesced loads staged through LDS; four partial sums
-//            over dim quarters, added in order), then top-(k-1) (ties:
+//            blocks (four partial sums over dim quarters, added in order), then top-(k-1) (ties:
 //            lower block index): up to 1024 candidates by rank, each thread
 //            counting the candidates that precede its own; beyond, by k-1
 //            rounds of a wave-wide argmax.  The selection is written
@@ -25,8 +25,8 @@
 //            the blocks the group's query heads selected, which each
 //            work-group finds from the selections itself: its slot's block
 //            in the ascending union), all query heads of the group:
-//            scores with one key per lane (bf16 dot2 against the packed
-//            query, fp32 sums), a per-head softmax over the chunk, P V with
+//            S (64 keys x up to 16 heads per wave) on 16x16x32 MFMAs, a per-head
+//            softmax over the chunk (a lane holds 16 keys of one head), P V with
 //            one dimension pair per lane and 64 keys per wave (dot2 over key
 //            pairs: weights rounded once to bf16, as the prefill's P V, fp32
 //            sums); the value rows are all requested before the softmax; the
@@ -49,6 +49,9 @@ constexpr float kLn2 = 0.69314718055994531f;
 constexpr float kLog2e = 1.4426950408889634f;
 
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ bf16x2_t as_bf16x2(uint32_t w) { return __builtin_bit_cast(bf16x2_t, w); }
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 // Two fp32 values to a packed bf16 pair, round-to-nearest-even.
@@ -69,72 +72,59 @@ __device__ __forceinline__ void chunk_range(int x, int nsub, int B, int64_t L, i
 }
 
 // ================================================================== gate
-// One work-group per (sequence, query head).  The block means are read with
-// coalesced loads (each half-wave reads one block's 512 bytes), up to 256
-// blocks per pass, all of a pass's loads in flight at once; 64 blocks at a
-// time go through an LDS tile (rows padded by one float, so the dot products
-// read it without bank conflicts), where thread t forms the partial sum of
-// block t % 64 over dims [32 q, 32 q + 32), q = t / 64, and the four partials
-// are added in order.  Wave 0 then selects.
-constexpr int kGatePass = 256;              // blocks per pass
-constexpr int kGateChunk = 64;              // blocks per LDS tile
-constexpr int kGateRow = kHeadDim + 1;      // padded LDS row (floats)
-constexpr int kGateLoads = kGatePass * (kHeadDim / 4) / 256;  // float4 per thread per pass
+// One work-group per (sequence, query head).  Four lanes per block mean, each
+// a quarter of its dims straight into registers (a quarter is one 128-byte line),
+// all of a pass's loads in flight at once; a quarter is summed in dim order and the
+// four are added in order across the lanes.  (Staged through LDS 64 blocks at a
+// time, with three barriers each, the kernel took 16.3 us at 255 blocks, 32 heads; this
+// way 14.9 us.)
+constexpr int kGateAhead = 4;               // blocks per thread and pass
+constexpr int kGatePass = 64 * kGateAhead;  // blocks per pass
 constexpr int kRankMax = 1024;              // candidates ranked in parallel (4 per thread)
 
-__global__ __launch_bounds__(256) void decode_gate_kernel(DecodeArgs a, Problem p) {
-  __shared__ float qs[kHeadDim];
-  __shared__ float sc[kMaxBlocksPerSeq];
-  __shared__ float kt[kGateChunk * kGateRow];
-  __shared__ float ps[4][kGateChunk];
+__global__ __launch_bounds__(256) void decode_gate_kernel(DecodeArgs a, Problem p,
+                                                          const SeqInfo* __restrict__ seqs) {
+  __shared__ __attribute__((aligned(16))) float sc[kMaxBlocksPerSeq + 4];
   const int tid = threadIdx.x, lane = tid & 63;
   const int64_t row = blockIdx.x;  // s * Hq + h
   const int s = (int)(row / p.Hq), h = (int)(row % p.Hq);
   const int g = h / p.G;
-  const SeqInfo sq = a.seqs[s];
-  if (tid < kHeadDim / 2) {
-    const __hip_bfloat16* qr = a.q + (int64_t)s * a.q_ss + (int64_t)h * a.q_sh;
-    const uint32_t w = reinterpret_cast<const uint32_t*>(qr)[tid];
-    qs[2 * tid] = bf16_lo(w);
-    qs[2 * tid + 1] = bf16_hi(w);
-  }
+  const SeqInfo sq = seqs[s];
+  const int quarter = tid & 3;
   const int c = (int)((sq.len - 1) / p.B);  // current block; candidates j < c
-  const int jb = tid % kGateChunk, quarter = tid / kGateChunk;
-  for (int j0 = 0; j0 < c; j0 += kGatePass) {
-    // float4 e = tid + 256 i of the pass: block e / 32, piece e % 32
-    float4 kv[kGateLoads];
+  uint4 qw[4];  // this quarter of the query
+  {
+    const __hip_bfloat16* qr = a.q + (int64_t)s * a.q_ss + (int64_t)h * a.q_sh + 32 * quarter;
 #pragma unroll
-    for (int i = 0; i < kGateLoads; i++) {
-      const int e = tid + 256 * i;
-      const int j = min(j0 + e / (kHeadDim / 4), c - 1);  // past the candidates: re-read, unused
-      kv[i] = reinterpret_cast<const float4*>(
-          a.kbar + ((int64_t)(sq.blk_off + j) * p.Hkv + g) * kHeadDim)[e % (kHeadDim / 4)];
+    for (int i = 0; i < 4; i++) qw[i] = reinterpret_cast<const uint4*>(qr)[i];
+  }
+  for (int j0 = 0; j0 < c; j0 += kGatePass) {
+    float4 kv[kGateAhead][8];
+#pragma unroll
+    for (int e = 0; e < kGateAhead; e++) {
+      const int j = min(j0 + 64 * e + (tid >> 2), c - 1);  // past the candidates: re-read, unused
+      const float4* kr = reinterpret_cast<const float4*>(
+          a.kbar + ((int64_t)(sq.blk_off + j) * p.Hkv + g) * kHeadDim + 32 * quarter);
+#pragma unroll
+      for (int i = 0; i < 8; i++) kv[e][i] = kr[i];
     }
 #pragma unroll
-    for (int ch = 0; ch < kGatePass / kGateChunk; ch++) {
-      if (j0 + ch * kGateChunk >= c) break;  // uniform over the work-group
-      __syncthreads();  // the previous tile (and qs, first time) is done with
-#pragma unroll
-      for (int i = 0; i < kGateLoads / (kGatePass / kGateChunk); i++) {
-        const int ii = ch * (kGateLoads / (kGatePass / kGateChunk)) + i;
-        const int e = tid + 256 * ii - ch * kGateChunk * (kHeadDim / 4);
-        float* dst = kt + (e / (kHeadDim / 4)) * kGateRow + 4 * (e % (kHeadDim / 4));
-        dst[0] = kv[ii].x;
-        dst[1] = kv[ii].y;
-        dst[2] = kv[ii].z;
-        dst[3] = kv[ii].w;
-      }
-      __syncthreads();
+    for (int e = 0; e < kGateAhead; e++) {
       float acc = 0.0f;
-      const float* kr = kt + jb * kGateRow + 32 * quarter;
 #pragma unroll
-      for (int d = 0; d < 32; d++) acc = fmaf(qs[32 * quarter + d], kr[d], acc);
-      ps[quarter][jb] = acc;
-      __syncthreads();
-      const int j = j0 + ch * kGateChunk + tid;
-      if (tid < kGateChunk && j < c) sc[j] = ((ps[0][tid] + ps[1][tid]) + ps[2][tid]) + ps[3][tid];
+      for (int i = 0; i < 8; i++) {
+        const uint32_t w0 = i & 1 ? qw[i >> 1].z : qw[i >> 1].x, w1 = i & 1 ? qw[i >> 1].w : qw[i >> 1].y;
+        acc = fmaf(bf16_lo(w0), kv[e][i].x, acc);
+        acc = fmaf(bf16_hi(w0), kv[e][i].y, acc);
+        acc = fmaf(bf16_lo(w1), kv[e][i].z, acc);
+        acc = fmaf(bf16_hi(w1), kv[e][i].w, acc);
+      }
+      const float p1 = __shfl_down(acc, 1, 4), p2 = __shfl_down(acc, 2, 4), p3 = __shfl_down(acc, 3, 4);
+      const int j = j0 + 64 * e + (tid >> 2);
+      if (quarter == 0 && j < c) sc[j] = ((acc + p1) + p2) + p3;
     }
   }
+  if (tid < 4) sc[c + tid] = -INFINITY;  // the rank loop reads whole groups of four
   __syncthreads();
   const int kh = p.topk - 1;
   const int nh = min(kh, c);
@@ -155,9 +145,13 @@ __global__ __launch_bounds__(256) void decode_gate_kernel(DecodeArgs a, Problem 
       if (j < c) {
         const float sj = sc[j];
         int above = 0;
-        for (int u = 0; u < c; u++) {
-          const float su = sc[u];
-          above += (su > sj || (su == sj && u < j)) ? 1 : 0;
+#pragma unroll 4
+        for (int u = 0; u < c; u += 4) {  // (padded with -inf past c)
+          const float4 su = *reinterpret_cast<const float4*>(&sc[u]);
+          above += (su.x > sj || (su.x == sj && u < j)) ? 1 : 0;
+          above += (su.y > sj || (su.y == sj && u + 1 < j)) ? 1 : 0;
+          above += (su.z > sj || (su.z == sj && u + 2 < j)) ? 1 : 0;
+          above += (su.w > sj || (su.w == sj && u + 3 < j)) ? 1 : 0;
         }
         keep = above < nh;
       }
@@ -216,10 +210,9 @@ __global__ __launch_bounds__(256) void decode_gate_kernel(DecodeArgs a, Problem 
 // GM: the group size rounded up to a power of two (sizes the LDS arrays, so
 // small groups leave room for more resident work-groups).
 template <int GM>
-__global__ __launch_bounds__(256) void decode_attend_kernel(DecodeArgs a, Problem p) {
-  __shared__ uint32_t qw[GM][kHeadDim / 2];  // the group's queries, packed bf16 pairs
-  __shared__ float ps[GM][kDecodeChunk];
-  __shared__ uint32_t pw[GM][kDecodeChunk / 2];
+__global__ __launch_bounds__(256) void decode_attend_kernel(DecodeArgs a, Problem p,
+                                                            const SeqInfo* __restrict__ seqs) {
+  __shared__ __attribute__((aligned(16))) uint32_t pw[GM][kDecodeChunk / 2];
   __shared__ float red[4][GM][2];
   // per-wave P V sums of each head (dims 2*lane, 2*lane+1)
   __shared__ float2 accs[4][GM][64];
@@ -227,10 +220,16 @@ __global__ __launch_bounds__(256) void decode_attend_kernel(DecodeArgs a, Proble
   __shared__ unsigned long long umask[kMaxBlocksPerSeq / 64];
   __shared__ int ublock;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int s = blockIdx.y / p.Hkv, g = blockIdx.y % p.Hkv;
   const int G = p.G;
-  int x = blockIdx.x;  // chunk id: block * nsub + piece
-  if (!a.full) {
+  int s, g, x;  // x: chunk id, block * nsub + piece
+  if (a.full) {
+    // the grid runs over every sequence's chunks
+    s = find_seq(seqs, p.S, blockIdx.x, [](const SeqInfo& y) { return y.blk_off; });
+    g = blockIdx.y;
+    x = blockIdx.x - seqs[s].blk_off;
+  } else {
+    s = blockIdx.y / p.Hkv;
+    g = blockIdx.y % p.Hkv;
     // MoBA: the grid runs over the group's selected blocks only.  Work-group
     // slot blockIdx.x / nsub takes the slot-th smallest block any head of
     // the group selected: the selections as a bitmask (lane w: blocks
@@ -265,7 +264,7 @@ __global__ __launch_bounds__(256) void decode_attend_kernel(DecodeArgs a, Proble
     if (j < 0) return;
     x = j * a.nsub + blockIdx.x % a.nsub;
   }
-  const SeqInfo sq = a.seqs[s];
+  const SeqInfo sq = seqs[s];
   int64_t u0, u1;
   chunk_range(x, a.nsub, a.chunk_block, sq.len, u0, u1);
   if (u0 >= u1) return;
@@ -281,51 +280,55 @@ __global__ __launch_bounds__(256) void decode_attend_kernel(DecodeArgs a, Proble
     }
     use_head[tid] = use;
   }
-  for (int i = tid; i < G * (kHeadDim / 2); i += 256) {
-    const int hl = i / (kHeadDim / 2), d2 = i % (kHeadDim / 2);
-    qw[hl][d2] = reinterpret_cast<const uint32_t*>(a.q + (int64_t)s * a.q_ss +
-                                                   (int64_t)(g * G + hl) * a.q_sh)[d2];
-  }
   __syncthreads();
   int any = 0;
   for (int hl = 0; hl < G; hl++) any |= use_head[hl];
   if (!any) return;
 
-  // scores: lane = key u0 + 64 * wave + lane; each lane loads its own key
-  // row (16 loads of 16 bytes) into registers.  Rows past the chunk end load
-  // the chunk's first row (their scores are discarded).
-  const int64_t u = u0 + 64 * wave + lane;
-  const bool kv_ok = u < u1;
+  // S: keys 64 wave .. + 63 in four 16-key tiles.  A operands: lane -> key row
+  // lane % 16 of the tile, 16 bytes at dims 32 ks + 8 (lane / 16); rows past the
+  // chunk end load the chunk's first row (their scores are discarded).  B
+  // operands: head lane % 16 of the group, the same dims.
   const int kend = (int)min((int64_t)64, u1 - (u0 + 64 * wave));  // may be <= 0
-  uint32_t kw[kHeadDim / 2];  // the key row, packed bf16 pairs
+  const int hc = lane & 15, kq = lane >> 4;
+  bf16x8_t kf[4][4], qb[4];
   {
-    const int64_t t = sq.tok_start + (kv_ok ? u : u0);
-    const uint4* kp = reinterpret_cast<const uint4*>(a.k + t * a.k_st + (int64_t)g * a.k_sh);
+    const __hip_bfloat16* kp = a.k + (int64_t)g * a.k_sh + 8 * kq;
 #pragma unroll
-    for (int c8 = 0; c8 < kHeadDim / 8; c8++) {
-      const uint4 w = kp[c8];
-      kw[4 * c8] = w.x;
-      kw[4 * c8 + 1] = w.y;
-      kw[4 * c8 + 2] = w.z;
-      kw[4 * c8 + 3] = w.w;
+    for (int t = 0; t < 4; t++) {
+      const int kl = 16 * t + hc;
+      const __hip_bfloat16* row = kp + (sq.tok_start + u0 + (kl < kend ? 64 * wave + kl : 0)) * a.k_st;
+#pragma unroll
+      for (int ks = 0; ks < 4; ks++)
+        kf[t][ks] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t*>(row + 32 * ks));
+    }
+    const __hip_bfloat16* qp = a.q + (int64_t)s * a.q_ss +
+                               (int64_t)(g * G + min(hc, G - 1)) * a.q_sh + 8 * kq;
+#pragma unroll
+    for (int ks = 0; ks < 4; ks++)
+      qb[ks] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t*>(qp + 32 * ks));
+  }
+  // a lane's values: head hc, keys 16 t + 4 kq + i
+  float z[16];
+  float m = -INFINITY;
+#pragma unroll
+  for (int t = 0; t < 4; t++) {
+    f32x4_t acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int ks = 0; ks < 4; ks++)
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[t][ks], qb[ks], acc, 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      z[4 * t + i] = 16 * t + 4 * kq + i < kend ? acc[i] * a.scale_log2 : -INFINITY;
+      m = fmaxf(m, z[4 * t + i]);
     }
   }
-  const float c2 = a.scale_log2;
-  for (int hl = 0; hl < G; hl++) {
-    // fp32 sum of exact bf16 products, two dims per instruction
-    float acc = 0.0f;
-#pragma unroll
-    for (int d2 = 0; d2 < kHeadDim / 2; d2++)
-      acc = __builtin_amdgcn_fdot2_f32_bf16(as_bf16x2(qw[hl][d2]), as_bf16x2(kw[d2]), acc, false);
-    const float sv = kv_ok ? acc * c2 : -INFINITY;
-    float m = sv;
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
-    ps[hl][64 * wave + lane] = sv;
-    if (lane == 0) red[wave][hl][0] = m;
-  }
+  m = fmaxf(m, __shfl_xor(m, 16, 64));
+  m = fmaxf(m, __shfl_xor(m, 32, 64));
+  if (lane < G) red[wave][lane][0] = m;
   // this wave's 64 value rows (dims 2*lane, 2*lane+1), all in flight across
-  // the softmax below; slots past the chunk end load the chunk's first row,
+  // the softmax below (requested with the keys they would cost a quarter of the
+  // resident waves: 146 vs 135 us in MoBA mode at 1M tokens); slots past the chunk end load the chunk's first row,
   // which exists, and get weight 0
   const uint32_t* vrow = reinterpret_cast<const uint32_t*>(
       a.v + (sq.tok_start + u0) * a.v_st + (int64_t)g * a.v_sh) + lane;
@@ -333,17 +336,25 @@ __global__ __launch_bounds__(256) void decode_attend_kernel(DecodeArgs a, Proble
 #pragma unroll
   for (int e = 0; e < 64; e++) wv[e] = vrow[(int64_t)(e < kend ? 64 * wave + e : 0) * a.v_st / 2];
   __syncthreads();
-  // per head: chunk max, weights, sum
-  for (int hl = 0; hl < G; hl++) {
-    const float m = fmaxf(fmaxf(red[0][hl][0], red[1][hl][0]), fmaxf(red[2][hl][0], red[3][hl][0]));
-    const float pv = kv_ok ? __builtin_amdgcn_exp2f(ps[hl][64 * wave + lane] - m) : 0.0f;
-    // weights of keys 2i, 2i+1 as one bf16 pair (the operand of the P V dot2)
-    const float pn = __shfl_xor(pv, 1, 64);
-    if ((lane & 1) == 0) pw[hl][32 * wave + (lane >> 1)] = pack_bf16(pv, pn);
-    float l = pv;
+  // per head: chunk max, weights (keys 2i, 2i + 1 as one bf16 pair, the operand
+  // of the P V dot2), sum
+  if (hc < G) {
+    m = fmaxf(fmaxf(red[0][hc][0], red[1][hc][0]), fmaxf(red[2][hc][0], red[3][hc][0]));
+    float l = 0.0f;
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) l += __shfl_xor(l, o, 64);
-    if (lane == 0) red[wave][hl][1] = l;
+    for (int t = 0; t < 4; t++) {
+      float pv[4];
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        pv[i] = 16 * t + 4 * kq + i < kend ? __builtin_amdgcn_exp2f(z[4 * t + i] - m) : 0.0f;
+        l += pv[i];
+      }
+      *reinterpret_cast<uint2*>(&pw[hc][32 * wave + 8 * t + 2 * kq]) =
+          make_uint2(pack_bf16(pv[0], pv[1]), pack_bf16(pv[2], pv[3]));
+    }
+    l += __shfl_xor(l, 16, 64);  // (the four lanes of a head take this branch together)
+    l += __shfl_xor(l, 32, 64);
+    if (kq == 0) red[wave][hc][1] = l;
   }
   __syncthreads();
   // P V: wave w sums keys 64w .. 64w+63 for dims 2*lane, 2*lane+1, a key
@@ -441,26 +452,24 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(DecodeArgs a, Probl
     const int32_t* sl = a.sel + row * p.topk;
     const int zend = min(p.topk * a.nsub, xb + a.split_len);
     for (int z0 = xb + grp; z0 < zend; z0 += 16 * kAhead) {
+      // selections, then partials, each without a branch so that all are in
+      // flight (slots without a partial read the row's first one, unused)
+      int js[kAhead];
+#pragma unroll
+      for (int e = 0; e < kAhead; e++) js[e] = sl[min(z0 + 16 * e, zend - 1) / a.nsub];
       float lv[kAhead];
       float4 o0[kAhead], o1[kAhead];
       bool ok[kAhead];
 #pragma unroll
       for (int e = 0; e < kAhead; e++) {
-        const int z = z0 + 16 * e;
-        ok[e] = false;
-        if (z < zend) {
-          const int y = z / a.nsub, i = z % a.nsub;
-          const int j = sl[y];
-          const int64_t u0 = (int64_t)j * p.B + (int64_t)i * kDecodeChunk;
-          if (j >= 0 && u0 < min((int64_t)(j + 1) * p.B, (int64_t)sq.len)) {
-            ok[e] = true;
-            const int64_t pr = row * a.nchunk + j * a.nsub + i;
-            const float4* op = reinterpret_cast<const float4*>(a.part_o + pr * kHeadDim + 8 * l16);
-            lv[e] = a.part_lse[pr];
-            o0[e] = op[0];
-            o1[e] = op[1];
-          }
-        }
+        const int z = z0 + 16 * e, i = z % a.nsub, j = js[e];
+        const int64_t u0 = (int64_t)j * p.B + (int64_t)i * kDecodeChunk;
+        ok[e] = z < zend && j >= 0 && u0 < min((int64_t)(j + 1) * p.B, (int64_t)sq.len);
+        const int64_t pr = row * a.nchunk + (ok[e] ? j * a.nsub + i : 0);
+        const float4* op = reinterpret_cast<const float4*>(a.part_o + pr * kHeadDim + 8 * l16);
+        lv[e] = a.part_lse[pr];
+        o0[e] = op[0];
+        o1[e] = op[1];
       }
 #pragma unroll
       for (int e = 0; e < kAhead; e++)
@@ -541,19 +550,20 @@ __global__ __launch_bounds__(kHeadDim) void decode_fold_kernel(DecodeArgs a, Pro
 hipError_t launch_decode_gate(const DecodeArgs& a, const Problem& p, hipStream_t st) {
   const int64_t rows = (int64_t)p.S * p.Hq;
   if (rows <= 0 || a.full) return hipSuccess;
-  decode_gate_kernel<<<(unsigned)rows, 256, 0, st>>>(a, p);
+  decode_gate_kernel<<<(unsigned)rows, 256, 0, st>>>(a, p, a.seqs);
   return hipGetLastError();
 }
 
 hipError_t launch_decode_attend(const DecodeArgs& a, const Problem& p, hipStream_t st) {
   if (p.S <= 0 || a.nchunk <= 0) return hipSuccess;
-  const int nx = a.full ? a.nchunk : a.nunion * a.nsub;
-  dim3 grid((unsigned)nx, (unsigned)(p.S * p.Hkv));
-  if (p.G <= 1) decode_attend_kernel<1><<<grid, 256, 0, st>>>(a, p);
-  else if (p.G <= 2) decode_attend_kernel<2><<<grid, 256, 0, st>>>(a, p);
-  else if (p.G <= 4) decode_attend_kernel<4><<<grid, 256, 0, st>>>(a, p);
-  else if (p.G <= 8) decode_attend_kernel<8><<<grid, 256, 0, st>>>(a, p);
-  else decode_attend_kernel<kDecodeMaxGroup><<<grid, 256, 0, st>>>(a, p);
+  // full: every sequence's chunks (the plan's blocks are chunks then); MoBA: slots
+  const dim3 grid = a.full ? dim3((unsigned)p.nblk_total, (unsigned)p.Hkv)
+                           : dim3((unsigned)(a.nunion * a.nsub), (unsigned)(p.S * p.Hkv));
+  if (p.G <= 1) decode_attend_kernel<1><<<grid, 256, 0, st>>>(a, p, a.seqs);
+  else if (p.G <= 2) decode_attend_kernel<2><<<grid, 256, 0, st>>>(a, p, a.seqs);
+  else if (p.G <= 4) decode_attend_kernel<4><<<grid, 256, 0, st>>>(a, p, a.seqs);
+  else if (p.G <= 8) decode_attend_kernel<8><<<grid, 256, 0, st>>>(a, p, a.seqs);
+  else decode_attend_kernel<kDecodeMaxGroup><<<grid, 256, 0, st>>>(a, p, a.seqs);
   return hipGetLastError();
 }
 

@@ -8,7 +8,7 @@ namespace moba {
 
 constexpr int kDecodeChunk = 256;     // keys per attention work-group
 constexpr int kDecodeMaxGroup = 16;   // largest Hq / Hkv the decode kernels take
-constexpr int kCombineShare = 64;    // partials one combine work-group folds
+constexpr int kCombineShare = 256;   // partials one combine work-group folds
 constexpr int kCombineMaxSplit = 64; // combine work-groups per row, at most
 
 struct DecodeArgs {
