@@ -30,7 +30,9 @@
 //          D-wave dP = dO . V^T, dS (with P from LDS) and dK^T += Q^T . dS:
 //          16 MFMAs each; the D-wave's dK product of a subtile runs one
 //          subtile late, beside the P-wave's exponentials of the next.  Each
-//          key has one owner, so dK and dV need neither atomics nor a merge.
+//          key has one owner, so dK and dV need neither atomics nor a merge;
+//          only where a batch has fewer key tiles than the chip CUs are a
+//          tile's rows shared out (kv_split), the shares summed in order.
 // P and dS enter the second products as bf16; every product accumulates in
 // fp32.  The key side forms dS from the bf16 P its dV product uses (the value
 // it receives from the pair's P-wave); the query side from its fp32 P.
@@ -450,10 +452,10 @@ __device__ __forceinline__ RowFetch row_fetch(const BwdArgs& a, const Problem& p
     f.rec = a.rec[L.bstart + x];
   } else if (x < L.nrows) {
     f.kind = 1;
-    const int y = (int)(x - L.nhist);
-    const int hl = y / L.nct;
-    f.t = L.k0 + (y - hl * L.nct);
-    f.h = L.g * p.G + hl;
+    const int y = (int)(x - L.nhist);  // token-major: a token's rows are one run of memory
+    const int tt = y / p.G;
+    f.t = L.k0 + tt;
+    f.h = L.g * p.G + (y - tt * p.G);
     f.ld = a.ld[(int64_t)f.h * p.T + f.t];
   } else {
     f.kind = 2;
@@ -593,6 +595,11 @@ __device__ __forceinline__ void ds_weights(const f32x16& dpv, const RowTab& R, i
   sb[1] = as_bf16x8(u32x4{w[4], w[5], w[6], w[7]});
 }
 
+// Chunks of one share of a row list.
+__device__ __forceinline__ int split_share(int64_t nrows, int nsplit) {
+  return (int)(((nrows + kChunk - 1) / kChunk + nsplit - 1) / nsplit);
+}
+
 // Work-group: 4 pairs of waves, each pair owning 32 keys.  The P-wave holds
 // K, computes S and P and accumulates dV^T; the D-wave holds V, computes dP
 // and dS (with the P-wave's P, passed through LDS with a per-pair flag for
@@ -603,6 +610,8 @@ __device__ __forceinline__ void ds_weights(const f32x16& dpv, const RowTab& R, i
 // 4 + (q + 2) % 4, so the two waves of a SIMD belong to different pairs and
 // neither waits on the other's progress (2.7% faster than pairing the two
 // waves of one SIMD, whose phases then lock together).
+// SPLIT: a work-group takes one of a.nsplit shares of its key tile's rows.
+template <bool SPLIT>
 __global__ __launch_bounds__(64 * kDkdvWaves, 1) void bwd_dkdv_kernel(BwdArgs a, Problem p) {
   __shared__ u32x4 lds[5 * kBufR];  // Q chunk x3 (dK runs a subtile late), dO chunk x2
   __shared__ RowTab R;
@@ -615,12 +624,13 @@ __global__ __launch_bounds__(64 * kDkdvWaves, 1) void bwd_dkdv_kernel(BwdArgs a,
   // role 0: P-wave, 1: D-wave (wave-uniform: scalar branches)
   const int role = __builtin_amdgcn_readfirstlane(wave >> 2), pair = (wave + 2 * role) & 3;
 
-  // work-group -> (kv-head, key tile): each XCD takes a contiguous run (the
-  // key tiles of one bin read the same rows), early blocks (longest row
-  // lists) first
+  // work-group -> (kv-head, key tile, share of its rows): each XCD takes a
+  // contiguous run (the key tiles of one bin read the same rows), early blocks
+  // (longest row lists) first
   const int64_t total = a.nktiles * p.Hkv;
   const int64_t per = gridDim.x / 8;
-  const int64_t wi = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
+  const int64_t wx = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
+  const int64_t wi = SPLIT ? wx / a.nsplit : wx;
   if (wi >= total) return;
   RowList L;
   L.g = (int)(wi / a.nktiles);
@@ -637,7 +647,14 @@ __global__ __launch_bounds__(64 * kDkdvWaves, 1) void bwd_dkdv_kernel(BwdArgs a,
   L.nhist = uniform64(L.nhist);
   L.bstart = uniform64(L.bstart);
   L.nrows = L.nhist + (int64_t)L.nct * p.G;
-  const int nch = (int)((L.nrows + kChunk - 1) / kChunk);
+  // this work-group's chunks: c0 .. c0 + nch - 1 of the list's
+  int c0 = 0, nch = (int)((L.nrows + kChunk - 1) / kChunk);
+  if constexpr (SPLIT) {
+    const int share = split_share(L.nrows, a.nsplit);
+    c0 = (int)(wx % a.nsplit) * share;
+    nch = min(share, nch - c0);
+    if (nch <= 0) return;
+  }
 
   // the pair's 32 keys; this wave's K (P-wave) or V (D-wave) as B operands
   const int kw0 = kt.k0 + 32 * pair;
@@ -709,8 +726,8 @@ __global__ __launch_bounds__(64 * kDkdvWaves, 1) void bwd_dkdv_kernel(BwdArgs a,
   // prologue: row tables of chunks 0 and 1, chunk 0 landed
   if (tid < kDkdvWaves / 2) pflag[tid] = 0;
   if (wave == 0) {
-    row_store(a, R, 0, lane, row_fetch(a, p, L, 0, lane));
-    if (nch > 1) row_store(a, R, 1, lane, row_fetch(a, p, L, 1, lane));
+    row_store(a, R, 0, lane, row_fetch(a, p, L, c0, lane));
+    if (nch > 1) row_store(a, R, 1, lane, row_fetch(a, p, L, c0 + 1, lane));
   }
   __syncthreads();
   dma_rows(0, lds, lds + 3 * kBufR);
@@ -729,20 +746,17 @@ __global__ __launch_bounds__(64 * kDkdvWaves, 1) void bwd_dkdv_kernel(BwdArgs a,
       const int cur = i & 1;
       RowFetch nf;
       const bool fetch = wave == 0 && i + 2 < nch;
-      if (fetch) nf = row_fetch(a, p, L, i + 2, lane);
+      if (fetch) nf = row_fetch(a, p, L, c0 + i + 2, lane);
       if (i + 1 < nch)
         dma_rows((i + 1) % kSlots, lds + ((i + 1) % 3) * kBufR, lds + (3 + (cur ^ 1)) * kBufR);
       const char* qr = reinterpret_cast<const char*>(lds + (i % 3) * kBufR);
       const char* dr = reinterpret_cast<const char*>(lds + (3 + cur) * kBufR);
       const int slot = i % kSlots;
-      // masks are needed where rows are missing (list end, partial key tile) or
-      // may precede a key: the first kKeysPerDkdv unrouted rows of each head
-      bool edge = (int64_t)(i + 1) * kChunk > L.nhist || !full;
-      if (edge && full) {
-        const int64_t x0 = (int64_t)i * kChunk - L.nhist;
-        const int off = x0 >= 0 ? (int)x0 % L.nct : 0;
-        edge = off < kKeysPerDkdv || off + kChunk > L.nct || x0 + L.nhist + kChunk > L.nrows;
-      }
+      // masks are needed where rows are missing (list end, partial key tile) or may
+      // precede a key (the unrouted rows of the key tile's own tokens)
+      const int64_t x1 = (int64_t)(c0 + i) * kChunk;  // the chunk's first row
+      const bool edge = !full || x1 + kChunk > L.nrows ||
+                        (x1 + kChunk > L.nhist && x1 < L.nhist + (int64_t)kKeysPerDkdv * p.G);
 #pragma unroll 1
       for (int st = 0; st < 2; st++) {
         if (!live) continue;
@@ -799,6 +813,19 @@ __global__ __launch_bounds__(64 * kDkdvWaves, 1) void bwd_dkdv_kernel(BwdArgs a,
 
   // -------------------------------------------------------------- epilogue
   if (!live || key >= kt.k1) return;
+  if constexpr (SPLIT) {
+    // this share's sums, unscaled: [share][key tile][dV, dK][key][dim]
+    float* part = a.kv_part + ((((wx % a.nsplit) * total + wi) * 2 + role) * kKeysPerDkdv +
+                               (32 * pair + qc)) * kHeadDim;
+#pragma unroll
+    for (int dt = 0; dt < 4; dt++)
+#pragma unroll
+      for (int r4 = 0; r4 < 4; r4++)
+        *reinterpret_cast<float4*>(part + 32 * dt + 8 * r4 + 4 * hh) =
+            make_float4(acc[dt][4 * r4], acc[dt][4 * r4 + 1], acc[dt][4 * r4 + 2],
+                        acc[dt][4 * r4 + 3]);
+    return;
+  }
   const float scl = role == 0 ? 1.0f : a.scale;
   __hip_bfloat16* dst = role == 0 ? static_cast<__hip_bfloat16*>(a.dv) + (int64_t)key * a.dv_st +
                                         (int64_t)L.g * a.dv_sh
@@ -813,6 +840,48 @@ __global__ __launch_bounds__(64 * kDkdvWaves, 1) void bwd_dkdv_kernel(BwdArgs a,
       w.y = pack_bf16(acc[dt][4 * r4 + 2] * scl, acc[dt][4 * r4 + 3] * scl);
       *reinterpret_cast<uint2*>(dst + 32 * dt + 8 * r4 + 4 * hh) = w;
     }
+}
+
+// Sums the shares of split row lists in order and writes dK and dV: 16 bytes of
+// every share per thread, work-group -> 8 keys of one key tile's dV (or dK).
+constexpr int kSumKeys = 256 / (kHeadDim / 4);
+__global__ __launch_bounds__(256) void bwd_dkdv_sum_kernel(BwdArgs a, Problem p) {
+  const int64_t total = a.nktiles * p.Hkv;
+  constexpr int kPerTile = kKeysPerDkdv / kSumKeys;
+  const int64_t wi = blockIdx.x / (2 * kPerTile);
+  const int role = blockIdx.x / kPerTile % 2;
+  const int kl = (int)(blockIdx.x % kPerTile) * kSumKeys + threadIdx.x / (kHeadDim / 4);
+  const int c4 = threadIdx.x % (kHeadDim / 4);
+  const int g = (int)(wi / a.nktiles);
+  const KeyTile kt = a.ktiles[wi % a.nktiles];
+  const int key = kt.k0 + kl;
+  if (key >= kt.k1) return;
+  // shares that hold rows, as the dK/dV work-groups count them
+  int64_t nrows = (int64_t)(kt.bend - kt.k0) * p.G;
+  if (a.bin_count) nrows += a.bin_count[(int64_t)g * p.nblk_total + kt.b];
+  const int share = split_share(nrows, a.nsplit);
+  const int n = ((int)((nrows + kChunk - 1) / kChunk) + share - 1) / share;
+  const float4* part = reinterpret_cast<const float4*>(
+      a.kv_part + ((wi * 2 + role) * kKeysPerDkdv + kl) * kHeadDim) + c4;
+  const int64_t stride = total * 2 * kKeysPerDkdv * (kHeadDim / 4);
+  float4 v[kMaxKvSplit];
+#pragma unroll
+  for (int x = 0; x < kMaxKvSplit; x++) v[x] = part[min(x, n - 1) * stride];
+  float4 t = v[0];
+#pragma unroll
+  for (int x = 1; x < kMaxKvSplit; x++)
+    if (x < n) {
+      t.x += v[x].x;
+      t.y += v[x].y;
+      t.z += v[x].z;
+      t.w += v[x].w;
+    }
+  const float scl = role == 0 ? 1.0f : a.scale;
+  __hip_bfloat16* dst =
+      role == 0 ? static_cast<__hip_bfloat16*>(a.dv) + (int64_t)key * a.dv_st + (int64_t)g * a.dv_sh
+                : static_cast<__hip_bfloat16*>(a.dk) + (int64_t)key * a.dk_st + (int64_t)g * a.dk_sh;
+  reinterpret_cast<uint2*>(dst)[c4] =
+      make_uint2(pack_bf16(t.x * scl, t.y * scl), pack_bf16(t.z * scl, t.w * scl));
 }
 
 }  // namespace
@@ -847,8 +916,15 @@ hipError_t launch_bwd_dq_cur(const BwdArgs& a, const Problem& p, hipStream_t st)
 hipError_t launch_bwd_dkdv(const BwdArgs& a, const Problem& p, hipStream_t st) {
   const int64_t total = a.nktiles * p.Hkv;
   if (total <= 0) return hipSuccess;
-  const int64_t grid = (total + 7) / 8 * 8;
-  bwd_dkdv_kernel<<<(unsigned)grid, 64 * kDkdvWaves, 0, st>>>(a, p);
+  const unsigned grid = (unsigned)((total * a.nsplit + 7) / 8 * 8);
+  if (a.nsplit == 1) {
+    bwd_dkdv_kernel<false><<<grid, 64 * kDkdvWaves, 0, st>>>(a, p);
+    return hipGetLastError();
+  }
+  bwd_dkdv_kernel<true><<<grid, 64 * kDkdvWaves, 0, st>>>(a, p);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  bwd_dkdv_sum_kernel<<<(unsigned)(total * 2 * (kKeysPerDkdv / kSumKeys)), 256, 0, st>>>(a, p);
   return hipGetLastError();
 }
 

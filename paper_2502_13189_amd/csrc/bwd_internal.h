@@ -9,6 +9,8 @@ namespace moba {
 constexpr int kDkdvWaves = 8;                       // waves per dK/dV work-group (two per SIMD)
 constexpr int kKeysPerDkdv = 32 * (kDkdvWaves / 2);  // keys per dK/dV work-group (32 per SIMD)
 
+constexpr int kMaxKvSplit = 8;                       // shares of a key tile's row list, at most
+
 // Keys [k0, k1) of global block b; the rows of tokens [k0, bend) attend them
 // without routing (the block's own rows; in a head block, those of the whole
 // head).  One dK/dV work-group per key tile and kv-head.
@@ -44,6 +46,8 @@ struct BwdArgs {
   int64_t ntiles;
   const KeyTile* ktiles;
   int64_t nktiles;
+  int nsplit;        // dK/dV work-groups per key tile, each a share of its rows
+  float* kv_part;    // nsplit > 1: [nsplit][nktiles * Hkv][2][kKeysPerDkdv][D] fp32
   int g0, g1;        // kv-heads of this chunk (dQ kernels)
   float scale_log2;  // log2(e) / sqrt(D)
   float scale;       // 1 / sqrt(D)
@@ -62,7 +66,7 @@ hipError_t launch_bwd_rec(const BwdArgs& a, const Problem& p, hipStream_t st);
 hipError_t launch_bwd_dq_hist(const BwdArgs& a, const Problem& p, int64_t grid, hipStream_t st);
 // Current-block dQ plus the history partials, written to dq.
 hipError_t launch_bwd_dq_cur(const BwdArgs& a, const Problem& p, hipStream_t st);
-// dK and dV of every key (all kv-heads).
+// dK and dV of every key (all kv-heads); with nsplit > 1 a second launch sums.
 hipError_t launch_bwd_dkdv(const BwdArgs& a, const Problem& p, hipStream_t st);
 
 }  // namespace moba

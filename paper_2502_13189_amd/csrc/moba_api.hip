@@ -852,6 +852,14 @@ moba_status moba_forward(const moba_tensor* q, const moba_tensor* k, const moba_
 
 namespace {
 
+// dK/dV work-groups per key tile: one work-group fills a CU, so with fewer key
+// tiles (of all kv-heads) than half of the 256 CUs, each tile's rows are shared out.
+// 1518 ragged tokens, 8/2 heads (26 key tiles): 88 us in one piece, 25 + 6 us in 8
+// with their sum.
+int kv_split(int64_t ktiles) {
+  return ktiles > 0 ? (int)std::min<int64_t>(kMaxKvSplit, std::max<int64_t>(1, 256 / ktiles)) : 1;
+}
+
 // The backward of moba_forward; with `dense`, of moba_dense_forward (each
 // sequence one block, top-1: the causal current block is the whole prefix).
 moba_status backward_impl(const moba_tensor* q, const moba_tensor* k, const moba_tensor* v,
@@ -923,7 +931,11 @@ moba_status backward_impl(const moba_tensor* q, const moba_tensor* k, const moba
     float* kbar; __hip_bfloat16* kterm; __hip_bfloat16* kt; int32_t* sel; RouteBuffers rb;
     float2* ld; int4* rec;
     float* dq_part;
+    float* kv_part;
   };
+  // shares of each dK/dV key tile's rows
+  const int64_t ktiles = (int64_t)pl->ktiles.size() * p.Hkv;
+  int nsplit = kv_split(ktiles);
   auto layout = [&](int nch, Bump* bp, Bufs* b) {
     b->kbar = bp->take<float>((int64_t)p.nblk_total * p.Hkv * kHeadDim);
     b->kterm = bp->take<__hip_bfloat16>((int64_t)3 * p.nblk_total * p.Hkv * kHeadDim);
@@ -940,15 +952,24 @@ moba_status backward_impl(const moba_tensor* q, const moba_tensor* k, const moba
     b->dq_part = bp->take<float>(routed ? (int64_t)nch * TG * kh * kHeadDim : 0);
     // the gate's counts are done with before the first dQ partial is written
     b->rb.gcount = p.gate_counts ? reinterpret_cast<int32_t*>(b->dq_part) : nullptr;
+    b->kv_part = bp->take<float>(nsplit > 1 ? nsplit * ktiles * 2 * kKeysPerDkdv * kHeadDim : 0);
   };
   const size_t limit = workspace_limit();
   int nch = 0;
   size_t need = 0;
-  for (int n = p.Hkv; n >= 1; n--) {
+  // (the shares only where the cap leaves room for them)
+  for (int n = p.Hkv; n >= 1 && nch == 0;) {
     Bump bp(nullptr);
     Bufs b{};
     layout(n, &bp, &b);
-    if (bp.off + kAlign <= limit) { nch = n; need = bp.off + kAlign; break; }
+    if (bp.off + kAlign <= limit) {
+      nch = n;
+      need = bp.off + kAlign;
+    } else if (nsplit > 1) {
+      nsplit = 1;
+    } else {
+      n--;
+    }
   }
   if (nch == 0) return MOBA_ERR_NO_MEMORY;
   nch = (int)ceil_div(p.Hkv, ceil_div(p.Hkv, nch));
@@ -979,6 +1000,8 @@ moba_status backward_impl(const moba_tensor* q, const moba_tensor* k, const moba
   a.ld = b.ld;
   a.rec = b.rec;
   a.dq_part = b.dq_part;
+  a.nsplit = nsplit;
+  a.kv_part = b.kv_part;
   a.tiles = d_tiles;
   a.ntiles = (int64_t)pl->tiles.size();
   a.ktiles = d_ktiles;

@@ -69,7 +69,6 @@ __global__ __launch_bounds__(256) void route_count_kernel(const int32_t* __restr
   const int g = blockIdx.y;
   const ChunkPos cp = chunk_pos(seqs, p, blockIdx.x);
   const SeqInfo sq = seqs[cp.s];
-  const int kh = p.topk - 1;
   for (int j = threadIdx.x; j < sq.nblk; j += 256) cnt[j] = 0;
   __syncthreads();
   // element e of the chunk: token cp.tl0 + e / (G topk), entry e % (G topk)

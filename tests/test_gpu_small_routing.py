@@ -1,7 +1,8 @@
 """Small batches let the gate count its selections and the scatter scan the
 counts; larger ones (here: the same batch with a filler sequence that brings it
 past 1024 bins) run the count and scan kernels.  Rows do not depend on the
-batch they are in, so both must give the same bits, forward and backward."""
+batch they are in, so both must give the same bits, forward and dQ; dK and dV are fp32
+sums that a small batch may take in shares, so they may round differently."""
 import pytest
 import torch
 
@@ -39,5 +40,8 @@ def test_small_routing_equals_general(seqlens, hq, hkv, B, topk, dtype):
         dout = inputs.make_dout(q.shape, dtype, T, device=DEV)
         gb = binding.backward(q, k, v, cu, B, topk, big, blse, dout)
         gs = binding.backward(qs, ks, vs, cus, B, topk, out, lse, dout[:T])
-        for name, x, y in zip(("dq", "dk", "dv"), gs, gb):
-            assert torch.equal(x, y[:T]), name
+        assert torch.equal(gs[0], gb[0][:T])
+        for name, x, y in zip(("dk", "dv"), gs[1:], gb[1:]):
+            # far fewer than all elements round to the other bf16 neighbour (2^-8 of the value)
+            x, y = x.double(), y[:T].double()
+            assert (x - y).norm() <= 2.0 ** -9 * y.norm(), name
