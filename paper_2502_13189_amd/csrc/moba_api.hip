@@ -3,7 +3,7 @@
 // declared in include/moba.h.
 //
 // moba_forward enqueues, on the caller's stream:
-//   pool -> [bf16: V^T pack] -> gate -> route (count, column scan, bin scan,
+//   pool [bf16: and V^T pack] -> gate -> route (count, column scan, bin scan,
 //   scatter) -> per chunk of kv-heads: history attention, then current-block
 //   attention (fp32 and short blocks: both in one launch), then the merge of
 //   the history partials, in place on the output.
@@ -805,14 +805,13 @@ moba_status moba_forward(const moba_tensor* q, const moba_tensor* k, const moba_
   a.tiles = d_tiles;
   a.ntiles = (int64_t)pl->tiles.size();
 
-  { Phase ph("pool", stream);
-    MOBA_LAUNCH(launch_pool(in.k.data, in.bf16, in.k.st, in.k.sh, d_seqs, p, kbar, fb.kterm,
-                            stream)); }
-  if (in.bf16) {
-    Phase ph("vt_pack", stream);
-    MOBA_LAUNCH(launch_vt_pack(static_cast<const __hip_bfloat16*>(in.v.data), in.v.st, in.v.sh,
-                               d_seqs, p, vt, stream));
-  }
+  { Phase ph("pool", stream);  // bf16: and the V^T pack
+    MOBA_LAUNCH(in.bf16 ? launch_pool_pack(static_cast<const __hip_bfloat16*>(in.k.data), in.k.st,
+                                           in.k.sh, static_cast<const __hip_bfloat16*>(in.v.data),
+                                           in.v.st, in.v.sh, d_seqs, p, true, kbar, fb.kterm, vt,
+                                           stream)
+                        : launch_pool(in.k.data, false, in.k.st, in.k.sh, d_seqs, p, kbar, nullptr,
+                                      stream)); }
   { Phase ph("gate", stream);
     MOBA_LAUNCH(launch_gate(in.q.data, in.bf16, in.q.st, in.q.sh, kbar, fb.kterm, d_seqs, p, sel,
                             nullptr, 0, rb.gcount, stream)); }
@@ -1020,12 +1019,10 @@ moba_status backward_impl(const moba_tensor* q, const moba_tensor* k, const moba
   }
 
   // the forward's selection and routing, recomputed
-  { Phase ph("pool", stream);
-    MOBA_LAUNCH(launch_pool(in.k.data, true, in.k.st, in.k.sh, d_seqs, p, b.kbar, b.kterm,
-                            stream)); }
-  { Phase ph("kt_pack", stream);
-    MOBA_LAUNCH(launch_vt_pack(static_cast<const __hip_bfloat16*>(in.k.data), in.k.st, in.k.sh,
-                               d_seqs, p, b.kt, stream)); }
+  { Phase ph("pool", stream);  // and the K^T pack
+    const __hip_bfloat16* kp = static_cast<const __hip_bfloat16*>(in.k.data);
+    MOBA_LAUNCH(launch_pool_pack(kp, in.k.st, in.k.sh, kp, in.k.st, in.k.sh, d_seqs, p, true, b.kbar,
+                                 b.kterm, b.kt, stream)); }
   { Phase ph("gate", stream);
     MOBA_LAUNCH(launch_gate(in.q.data, true, in.q.st, in.q.sh, b.kbar, b.kterm, d_seqs, p, b.sel,
                             nullptr, 0, b.rb.gcount, stream)); }
@@ -1127,8 +1124,8 @@ moba_status dense_forward_impl(const Inputs& in, const View& vo, moba_tensor* ls
   a.g1 = p.Hkv;
   if (in.bf16) {
     Phase ph("vt_pack", stream);
-    MOBA_LAUNCH(launch_vt_pack(static_cast<const __hip_bfloat16*>(in.v.data), in.v.st, in.v.sh,
-                               d_seqs, p, vt, stream));
+    MOBA_LAUNCH(launch_pool_pack(nullptr, 0, 0, static_cast<const __hip_bfloat16*>(in.v.data),
+                                 in.v.st, in.v.sh, d_seqs, p, false, nullptr, nullptr, vt, stream));
   }
   { Phase ph("dense", stream);
     MOBA_LAUNCH(in.bf16 ? launch_attn_causal_bf16(true, a, p, stream)

@@ -1,15 +1,21 @@
 // Block mean-pool of the keys and the packed V^T layout of the MFMA kernels.
 //
-// Pool (Eq. 6; Algorithm 1 mean_pool): one work-group per (global block,
-// kv-head).  256 threads = 16 token rows x 16 lanes; each lane owns 8
-// consecutive dims and walks the block's tokens with stride 16, reading a
-// 256-byte key row per 16 lanes (coalesced).  Sums are kept in fp64 and
-// reduced across the 16 rows in a fixed order, so the result is the block
-// mean rounded once to fp32 and is bit-reproducible.
+// Both are one pass over memory and independent of each other, so a call that
+// needs both makes one launch: pool work-groups first, then pack work-groups.
 //
-// V^T pack: one work-group per (64-key tile of a sequence, kv-head).  The
-// tile's 64 x 128 values are staged in LDS and written back as 128 rows
-// (dims) of 64 keys, with the keys of every 16-key group stored in the order
+// Pool (Eq. 6; Algorithm 1 mean_pool): one work-group per (global block,
+// kv-head).  1024 threads = 64 token rows x 16 lanes; each lane owns 8
+// consecutive dims and walks the block's tokens with stride 64, four loads in
+// flight, reading a 256-byte key row per 16 lanes (coalesced).  Sums are kept in fp64
+// and reduced across the rows in a fixed order, so the result is the block mean
+// rounded once to fp32 and is bit-reproducible.  With 16 rows and one load in
+// flight per work-group, a launch of few blocks was bound by latency: 32K tokens, 8
+// heads, B = 2048 (128 work-groups): 72 -> 27 us, K^T pack included (12 us before);
+// 8192 tokens, 32 heads, B = 512: 24 us and 28 for the pack -> 40 us for both.
+//
+// V^T pack: four waves per (64-key tile of a sequence, kv-head), each 32 dims and
+// without a barrier.  A wave's 64 x 32 values are staged in LDS and written back as
+// 32 rows (dims) of 64 keys, with the keys of every 16-key group stored in the order
 // 0-3, 8-11, 4-7, 12-15.  That order is the k-slot order in which the
 // attention kernel's P^T operand holds keys after the QK^T MFMA (see
 // attn_mfma.hip), so each lane reads its 8 keys as one 16-byte LDS load.
@@ -45,45 +51,70 @@ struct Load8<float> {
   }
 };
 
+constexpr int kThreads = 1024;
+constexpr int kPoolRows = kThreads / 16;  // token rows a pool work-group reads at a time
+constexpr int kPoolAhead = 4;             // loads in flight per thread
+constexpr int kPackTiles = kThreads / 256;  // tiles per pack work-group, four waves each
+constexpr int kPackRow = 32 + 2;
+
 // kterm (nullable): the block keys split exactly into three bf16 planes,
 // kbar = hi + mid + lo, each plane [nblk_total, Hkv, D] (read by the
 // matrix-core gate).
 template <typename T>
-__global__ __launch_bounds__(256) void pool_kernel(const T* __restrict__ k, int64_t k_st, int64_t k_sh,
-                                                   const SeqInfo* __restrict__ seqs, int S, int B,
-                                                   int Hkv, int nblk_total, float* __restrict__ kbar,
-                                                   __hip_bfloat16* __restrict__ kterm) {
-  __shared__ double red[16][kHeadDim];
-  const int b = blockIdx.x;
-  const int g = blockIdx.y;
-  const int s = find_seq(seqs, S, b, [](const SeqInfo& x) { return x.blk_off; });
+__device__ __forceinline__ void pool_block(const T* __restrict__ k, int64_t k_st, int64_t k_sh,
+                                           const SeqInfo* __restrict__ seqs, const Problem& p, int b,
+                                           int g, float* __restrict__ kbar,
+                                           __hip_bfloat16* __restrict__ kterm,
+                                           double (*red)[kHeadDim]) {
+  const int s = find_seq(seqs, p.S, b, [](const SeqInfo& x) { return x.blk_off; });
   const SeqInfo sq = seqs[s];
   const int j = b - sq.blk_off;
-  const int64_t t0 = (int64_t)sq.tok_start + (int64_t)j * B;
-  const int64_t t1 = (int64_t)sq.tok_start + min((int64_t)(j + 1) * B, (int64_t)sq.len);
+  const int64_t t0 = (int64_t)sq.tok_start + (int64_t)j * p.B;
+  const int n = (int)min((int64_t)p.B, (int64_t)sq.len - (int64_t)j * p.B);
   const int row = threadIdx.x >> 4;
   const int d0 = (threadIdx.x & 15) * 8;
+  const T* src = k + t0 * k_st + (int64_t)g * k_sh + d0;
   double acc[8];
 #pragma unroll
   for (int i = 0; i < 8; i++) acc[i] = 0.0;
-  for (int64_t t = t0 + row; t < t1; t += 16) {
+  int t = row;
+  for (; t + (kPoolAhead - 1) * kPoolRows < n; t += kPoolAhead * kPoolRows) {
+    float f[kPoolAhead][8];
+#pragma unroll
+    for (int e = 0; e < kPoolAhead; e++)
+      Load8<T>::run(src + (int64_t)(t + e * kPoolRows) * k_st, f[e]);
+#pragma unroll
+    for (int e = 0; e < kPoolAhead; e++)
+#pragma unroll
+      for (int i = 0; i < 8; i++) acc[i] += (double)f[e][i];
+  }
+  for (; t < n; t += kPoolRows) {
     float f[8];
-    Load8<T>::run(k + t * k_st + (int64_t)g * k_sh + d0, f);
+    Load8<T>::run(src + (int64_t)t * k_st, f);
 #pragma unroll
     for (int i = 0; i < 8; i++) acc[i] += (double)f[i];
   }
+  // the wave's four rows, then the 16 waves
 #pragma unroll
-  for (int i = 0; i < 8; i++) red[row][d0 + i] = acc[i];
+  for (int i = 0; i < 8; i++) {
+    acc[i] += __shfl_xor(acc[i], 16, 64);
+    acc[i] += __shfl_xor(acc[i], 32, 64);
+  }
+  const int wave = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) < 16) {
+#pragma unroll
+    for (int i = 0; i < 8; i++) red[wave][d0 + i] = acc[i];
+  }
   __syncthreads();
   if (threadIdx.x < kHeadDim) {
     double sum = 0.0;
 #pragma unroll
-    for (int r = 0; r < 16; r++) sum += red[r][threadIdx.x];
-    const float m = (float)(sum / (double)(t1 - t0));
-    const int64_t o = ((int64_t)b * Hkv + g) * kHeadDim + threadIdx.x;
+    for (int r = 0; r < kThreads / 64; r++) sum += red[r][threadIdx.x];
+    const float m = (float)(sum / (double)n);
+    const int64_t o = ((int64_t)b * p.Hkv + g) * kHeadDim + threadIdx.x;
     kbar[o] = m;
     if (kterm) {
-      const int64_t plane = (int64_t)nblk_total * Hkv * kHeadDim;
+      const int64_t plane = (int64_t)p.nblk_total * p.Hkv * kHeadDim;
       const __hip_bfloat16 hi = __float2bfloat16(m);
       const float r1 = m - __bfloat162float(hi);
       const __hip_bfloat16 mid = __float2bfloat16(r1);
@@ -101,39 +132,40 @@ __device__ __forceinline__ int packed_key(int p) {
   return grp + 8 * (jj >> 2) + 4 * half + (jj & 3);
 }
 
-__global__ __launch_bounds__(256) void vt_pack_kernel(const __hip_bfloat16* __restrict__ v,
-                                                      int64_t v_st, int64_t v_sh,
-                                                      const SeqInfo* __restrict__ seqs, int S,
-                                                      int64_t vt_tiles,
-                                                      __hip_bfloat16* __restrict__ vt) {
-  __shared__ uint16_t tile[kKeyTile][kHeadDim + 2];
-  const int64_t idx = blockIdx.x;
-  const int g = blockIdx.y;
-  const int s = find_seq(seqs, S, idx, [](const SeqInfo& x) { return x.vt_tile_off; });
+// Dims 32 quarter .. + 31 of tile idx (< vt_tiles) of kv-head g, by one wave.
+__device__ __forceinline__ void pack_tile(const __hip_bfloat16* __restrict__ v, int64_t v_st,
+                                          int64_t v_sh, const SeqInfo* __restrict__ seqs,
+                                          const Problem& p, int64_t idx, int g, int quarter,
+                                          __hip_bfloat16* __restrict__ vt,
+                                          uint16_t (*tile)[kPackRow]) {
+  const int lane = threadIdx.x & 63;
+  const int s = find_seq(seqs, p.S, idx, [](const SeqInfo& x) { return x.vt_tile_off; });
   const SeqInfo sq = seqs[s];
   const int i = (int)(idx - sq.vt_tile_off);
-  // stage 64 keys x 128 dims: 1024 chunks of 8 values, 4 per thread
+  // stage 64 keys x 32 dims: 4 lanes per key, 16 keys per load
+  uint4 u[4];
 #pragma unroll
   for (int x = 0; x < 4; x++) {
-    const int c = threadIdx.x + 256 * x;
-    const int r = c >> 4, col = (c & 15) * 8;
-    const int local = i * kKeyTile + r;
-    uint4 u = make_uint4(0, 0, 0, 0);
+    const int local = i * kKeyTile + 16 * x + (lane >> 2);
+    u[x] = make_uint4(0, 0, 0, 0);
     if (local < sq.len)
-      u = *reinterpret_cast<const uint4*>(v + ((int64_t)sq.tok_start + local) * v_st +
-                                          (int64_t)g * v_sh + col);
-    const uint32_t w[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-    for (int e = 0; e < 4; e++) {
-      tile[r][col + 2 * e] = (uint16_t)(w[e] & 0xffffu);
-      tile[r][col + 2 * e + 1] = (uint16_t)(w[e] >> 16);
-    }
+      u[x] = *reinterpret_cast<const uint4*>(v + ((int64_t)sq.tok_start + local) * v_st +
+                                             (int64_t)g * v_sh + 32 * quarter + 8 * (lane & 3));
   }
-  __syncthreads();
-  __hip_bfloat16* dst = vt + ((int64_t)g * vt_tiles + idx) * (kKeyTile * kHeadDim);
 #pragma unroll
   for (int x = 0; x < 4; x++) {
-    const int c = threadIdx.x + 256 * x;
+    uint32_t* dst = reinterpret_cast<uint32_t*>(&tile[16 * x + (lane >> 2)][8 * (lane & 3)]);
+    dst[0] = u[x].x;
+    dst[1] = u[x].y;
+    dst[2] = u[x].z;
+    dst[3] = u[x].w;
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");  // the wave's own writes, no barrier
+  __hip_bfloat16* dst = vt + ((int64_t)g * p.vt_tiles + idx) * (kKeyTile * kHeadDim) +
+                        32 * quarter * kKeyTile;
+#pragma unroll
+  for (int x = 0; x < 4; x++) {
+    const int c = lane + 64 * x;
     const int d = c >> 3, p0 = (c & 7) * 8;
     uint32_t w[4];
 #pragma unroll
@@ -146,27 +178,59 @@ __global__ __launch_bounds__(256) void vt_pack_kernel(const __hip_bfloat16* __re
   }
 }
 
+// Work-groups [0, npool): pool (block, kv-head); then pack (kPackTiles tiles, kv-head).
+template <typename T, bool PACK>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8)))
+void pool_pack_kernel(
+    const T* __restrict__ k, int64_t k_st, int64_t k_sh, const __hip_bfloat16* __restrict__ v,
+    int64_t v_st, int64_t v_sh, const SeqInfo* __restrict__ seqs, Problem p, uint32_t npool,
+    float* __restrict__ kbar, __hip_bfloat16* __restrict__ kterm, __hip_bfloat16* __restrict__ vt) {
+  constexpr size_t kPoolLds = sizeof(double) * (kThreads / 64) * kHeadDim;
+  constexpr size_t kPackLds = sizeof(uint16_t) * (kThreads / 64) * kKeyTile * kPackRow;
+  __shared__ __attribute__((aligned(16))) char lds[PACK && kPackLds > kPoolLds ? kPackLds : kPoolLds];
+  if (blockIdx.x < npool) {
+    pool_block<T>(k, k_st, k_sh, seqs, p, (int)(blockIdx.x % (uint32_t)p.nblk_total),
+                  (int)(blockIdx.x / (uint32_t)p.nblk_total), kbar, kterm,
+                  reinterpret_cast<double(*)[kHeadDim]>(lds));
+    return;
+  }
+  if constexpr (PACK) {
+    const uint32_t per = (uint32_t)((p.vt_tiles + kPackTiles - 1) / kPackTiles);
+    const uint32_t y = blockIdx.x - npool;
+    const int wave = threadIdx.x >> 6;
+    const int64_t idx = (int64_t)(y % per) * kPackTiles + (wave >> 2);
+    if (idx < p.vt_tiles)
+      pack_tile(v, v_st, v_sh, seqs, p, idx, (int)(y / per), wave & 3, vt,
+                reinterpret_cast<uint16_t(*)[kPackRow]>(lds) + wave * kKeyTile);
+  }
+}
+
 }  // namespace
 
 hipError_t launch_pool(const void* k, bool bf16, int64_t k_st, int64_t k_sh, const SeqInfo* seqs,
                        const Problem& p, float* kbar, __hip_bfloat16* kterm, hipStream_t st) {
   if (p.nblk_total == 0) return hipSuccess;
-  dim3 grid(p.nblk_total, p.Hkv);
+  const uint32_t npool = (uint32_t)p.nblk_total * (uint32_t)p.Hkv;
   if (bf16)
-    pool_kernel<__hip_bfloat16><<<grid, 256, 0, st>>>(
-        static_cast<const __hip_bfloat16*>(k), k_st, k_sh, seqs, p.S, p.B, p.Hkv, p.nblk_total,
-        kbar, kterm);
+    pool_pack_kernel<__hip_bfloat16, false><<<npool, kThreads, 0, st>>>(
+        static_cast<const __hip_bfloat16*>(k), k_st, k_sh, nullptr, 0, 0, seqs, p, npool, kbar,
+        kterm, nullptr);
   else
-    pool_kernel<float><<<grid, 256, 0, st>>>(static_cast<const float*>(k), k_st, k_sh, seqs, p.S,
-                                             p.B, p.Hkv, p.nblk_total, kbar, kterm);
+    pool_pack_kernel<float, false><<<npool, kThreads, 0, st>>>(
+        static_cast<const float*>(k), k_st, k_sh, nullptr, 0, 0, seqs, p, npool, kbar, kterm,
+        nullptr);
   return hipGetLastError();
 }
 
-hipError_t launch_vt_pack(const __hip_bfloat16* v, int64_t v_st, int64_t v_sh, const SeqInfo* seqs,
-                          const Problem& p, __hip_bfloat16* vt, hipStream_t st) {
+hipError_t launch_pool_pack(const __hip_bfloat16* k, int64_t k_st, int64_t k_sh,
+                            const __hip_bfloat16* v, int64_t v_st, int64_t v_sh,
+                            const SeqInfo* seqs, const Problem& p, bool pool, float* kbar,
+                            __hip_bfloat16* kterm, __hip_bfloat16* vt, hipStream_t st) {
   if (p.vt_tiles == 0) return hipSuccess;
-  dim3 grid((unsigned)p.vt_tiles, p.Hkv);
-  vt_pack_kernel<<<grid, 256, 0, st>>>(v, v_st, v_sh, seqs, p.S, p.vt_tiles, vt);
+  const uint32_t npool = pool ? (uint32_t)p.nblk_total * (uint32_t)p.Hkv : 0;
+  const uint32_t npack = (uint32_t)((p.vt_tiles + kPackTiles - 1) / kPackTiles) * (uint32_t)p.Hkv;
+  pool_pack_kernel<__hip_bfloat16, true><<<npool + npack, kThreads, 0, st>>>(
+      k, k_st, k_sh, v, v_st, v_sh, seqs, p, npool, kbar, kterm, vt);
   return hipGetLastError();
 }
 
