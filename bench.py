@@ -344,7 +344,9 @@ def run_backward(args):
     binding.profile_enable(False)
     phases = binding.profile_read()
     cur, hist, _ = attended_keys(w.seqlens, w.block_size, w.topk)
-    causal, routed = launch_keys(w.seqlens, w.block_size, w.topk, w.hq)
+    # (the backward routes every row below top-4)
+    causal, routed = (launch_keys(w.seqlens, w.block_size, w.topk, w.hq) if w.topk >= 4
+                      else (cur, hist))
     pairs = w.hq * (cur + hist)
     flop = 10.0 * w.d * pairs
     tflops = flop / (ms * 1e-3) / 1e12

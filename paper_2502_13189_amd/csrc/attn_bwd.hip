@@ -452,10 +452,10 @@ __device__ __forceinline__ RowFetch row_fetch(const BwdArgs& a, const Problem& p
     f.rec = a.rec[L.bstart + x];
   } else if (x < L.nrows) {
     f.kind = 1;
-    const int y = (int)(x - L.nhist);  // token-major: a token's rows are one run of memory
-    const int tt = y / p.G;
-    f.t = L.k0 + tt;
-    f.h = L.g * p.G + (y - tt * p.G);
+    const int y = (int)(x - L.nhist);
+    const int hl = y / L.nct;
+    f.t = L.k0 + (y - hl * L.nct);
+    f.h = L.g * p.G + hl;
     f.ld = a.ld[(int64_t)f.h * p.T + f.t];
   } else {
     f.kind = 2;
@@ -752,11 +752,7 @@ __global__ __launch_bounds__(64 * kDkdvWaves, 1) void bwd_dkdv_kernel(BwdArgs a,
       const char* qr = reinterpret_cast<const char*>(lds + (i % 3) * kBufR);
       const char* dr = reinterpret_cast<const char*>(lds + (3 + cur) * kBufR);
       const int slot = i % kSlots;
-      // masks are needed where rows are missing (list end, partial key tile) or may
-      // precede a key (the unrouted rows of the key tile's own tokens)
-      const int64_t x1 = (int64_t)(c0 + i) * kChunk;  // the chunk's first row
-      const bool edge = !full || x1 + kChunk > L.nrows ||
-                        (x1 + kChunk > L.nhist && x1 < L.nhist + (int64_t)kKeysPerDkdv * p.G);
+      const bool edge = (int64_t)(c0 + i + 1) * kChunk > L.nhist || !full;
 #pragma unroll 1
       for (int st = 0; st < 2; st++) {
         if (!live) continue;

@@ -208,7 +208,8 @@ moba_status read_cu(const moba_tensor* cu, int64_t T, hipStream_t stream,
 }
 
 // ------------------------------------------------------------- planning
-enum TileMode { kTilesNone = 0, kTilesCur = 1, kTilesDense = 2 };
+// kTilesBwd: kTilesCur without head blocks (the backward of a small top-k).
+enum TileMode { kTilesNone = 0, kTilesCur = 1, kTilesDense = 2, kTilesBwd = 3 };
 
 struct Plan {
   Problem p{};
@@ -239,6 +240,8 @@ int head_blocks(int64_t L, int G, int Hkv, int B, int topk) {
 // B = 0 means "one block per sequence" (dense attention).
 void build_plan(const std::vector<int32_t>& cu, int Hq, int Hkv, int B, int topk, TileMode mode,
                 int tile_rows, Plan* pl) {
+  const bool heads = mode == kTilesCur;
+  if (mode == kTilesBwd) mode = kTilesCur;
   Problem& p = pl->p;
   const int S = (int)cu.size() - 1;
   p.T = cu[S];
@@ -270,7 +273,7 @@ void build_plan(const std::vector<int32_t>& cu, int Hq, int Hkv, int B, int topk
     q.gate_off = (int32_t)gate;
     q.rc_off = (int32_t)rc;
     q.hist_off = hw;
-    q.head = mode == kTilesCur ? head_blocks(L, p.G, Hkv, B, topk) : 1;
+    q.head = heads ? head_blocks(L, p.G, Hkv, B, topk) : 1;
     blk += nb;
     vt += ceil_div(L, kKeyTile);
     gate += ceil_div(L, p.gate_tw);
@@ -416,7 +419,7 @@ struct PlanSlot {
   bool pending = false;      // `uploaded` recorded after the last copy
   uint64_t last_use = 0;
 };
-constexpr int kPlanSlots = 4;  // e.g. forward/backward, decode, and the step-level calls
+constexpr int kPlanSlots = 6;  // e.g. forward, backward, their dense ones, decode, step-level calls
 
 struct DevCache {
   void* ws = nullptr;
@@ -851,6 +854,14 @@ moba_status moba_forward(const moba_tensor* q, const moba_tensor* k, const moba_
 
 namespace {
 
+// The backward takes the forward's head blocks from this top-k on.  They spare it
+// (topk - 1) / 2 fp32 dQ partials per head row but make its causal dQ tiles long, one
+// work-group per CU.  Forward + backward without and with them, 32/8 heads: 16K
+// tokens, B = 256, top-16: 7.60 -> 7.22 ms; 32K, B = 512, top-8: 12.25 -> 11.97; 16K, B =
+// 1024, top-4: 4.69 -> 4.67; 32K, B = 2048, top-3: 12.18 -> 12.30; 8K tokens, 32 heads, B =
+// 128, top-3: 1.095 -> 1.103.
+constexpr int kBwdHeadTopk = 4;
+
 // dK/dV work-groups per key tile: one work-group fills a CU, so with fewer key
 // tiles (of all kv-heads) than half of the 256 CUs, each tile's rows are shared out.
 // 1518 ragged tokens, 8/2 heads (26 key tiles): 88 us in one piece, 25 + 6 us in 8
@@ -915,7 +926,8 @@ moba_status backward_impl(const moba_tensor* q, const moba_tensor* k, const moba
   const SeqInfo* d_seqs;
   const CausalTile* d_tiles;
   const KeyTile* d_ktiles;
-  if ((st = get_plan(dc, stream, in.cu, in.Hq, in.Hkv, block_size, kk, kTilesCur, kTileRowsMfma, &pl,
+  const TileMode tiles = kk < kBwdHeadTopk ? kTilesBwd : kTilesCur;
+  if ((st = get_plan(dc, stream, in.cu, in.Hq, in.Hkv, block_size, kk, tiles, kTileRowsMfma, &pl,
                      &d_seqs, &d_tiles, &d_ktiles)) != MOBA_OK)
     return st;
   Problem p = pl->p;  // the selection is private here: kv-head-major
