@@ -9,7 +9,7 @@
 // far below the ridge of either the matrix cores or the vector ALUs, so it is
 // bound by HBM and the loads decide: a probe of the bare loads ran at 4.6-5.0
 // TB/s with one key row per lane and at 5.8-6.1 TB/s with K as matrix operands (16
-// rows x 64 bytes per load) and V one row per load, the layouts used here; so S
+// rows x 64 bytes per load) and V by whole rows, the layouts used here; so S
 // comes from the matrix cores, P V from packed bf16 dot products.  In MoBA
 // mode only the selected blocks are touched.
 //
@@ -27,7 +27,7 @@
 //            in the ascending union), all query heads of the group:
 //            S (64 keys x up to 16 heads per wave) on 16x16x32 MFMAs, a per-head
 //            softmax over the chunk (a lane holds 16 keys of one head), P V with
-//            one dimension pair per lane and 64 keys per wave (dot2 over key
+//            8 dims and 16 of the wave's 64 keys per lane (dot2 over key
 //            pairs: weights rounded once to bf16, as the prefill's P V, fp32
 //            sums); the value rows are all requested before the softmax; the
 //            normalised partial and its lse go to the workspace; a head that
@@ -215,7 +215,7 @@ __global__ __launch_bounds__(256) void decode_attend_kernel(DecodeArgs a, Proble
   __shared__ __attribute__((aligned(16))) uint32_t pw[GM][kDecodeChunk / 2];
   __shared__ float red[4][GM][2];
   // per-wave P V sums of each head (dims 2*lane, 2*lane+1)
-  __shared__ float2 accs[4][GM][64];
+  __shared__ __attribute__((aligned(16))) float2 accs[4][GM][64];
   __shared__ int use_head[GM];
   __shared__ unsigned long long umask[kMaxBlocksPerSeq / 64];
   __shared__ int ublock;
@@ -326,18 +326,23 @@ __global__ __launch_bounds__(256) void decode_attend_kernel(DecodeArgs a, Proble
   m = fmaxf(m, __shfl_xor(m, 16, 64));
   m = fmaxf(m, __shfl_xor(m, 32, 64));
   if (lane < G) red[wave][lane][0] = m;
-  // this wave's 64 value rows (dims 2*lane, 2*lane+1), all in flight across
-  // the softmax below (requested with the keys they would cost a quarter of the
-  // resident waves: 146 vs 135 us in MoBA mode at 1M tokens); slots past the chunk end load the chunk's first row,
-  // which exists, and get weight 0
-  const uint32_t* vrow = reinterpret_cast<const uint32_t*>(
-      a.v + (sq.tok_start + u0) * a.v_st + (int64_t)g * a.v_sh) + lane;
-  uint32_t wv[64];
+  // this wave's 64 value rows, 16 lanes x 16 bytes per row and four rows per load
+  // (keys 4 i + kq at dims 8 hc .. + 7), all in flight across the softmax below
+  // (requested with the keys they would cost a quarter of the resident waves: 146 vs
+  // 135 us in MoBA mode at 1M tokens); slots past the chunk end load the chunk's first
+  // row, which exists, and get weight 0
+  uint4 wv[16];
+  {
+    const __hip_bfloat16* vp = a.v + (sq.tok_start + u0) * a.v_st + (int64_t)g * a.v_sh + 8 * hc;
 #pragma unroll
-  for (int e = 0; e < 64; e++) wv[e] = vrow[(int64_t)(e < kend ? 64 * wave + e : 0) * a.v_st / 2];
+    for (int i = 0; i < 16; i++) {
+      const int kl = 4 * i + kq;
+      wv[i] = *reinterpret_cast<const uint4*>(vp + (int64_t)(kl < kend ? 64 * wave + kl : 0) * a.v_st);
+    }
+  }
   __syncthreads();
-  // per head: chunk max, weights (keys 2i, 2i + 1 as one bf16 pair, the operand
-  // of the P V dot2), sum
+  // per head: chunk max, weights (keys 8 j + e and 8 j + 4 + e as one bf16 pair, word 4
+  // j + e: the keys a lane holds in two value loads), sum
   if (hc < G) {
     m = fmaxf(fmaxf(red[0][hc][0], red[1][hc][0]), fmaxf(red[2][hc][0], red[3][hc][0]));
     float l = 0.0f;
@@ -349,37 +354,63 @@ __global__ __launch_bounds__(256) void decode_attend_kernel(DecodeArgs a, Proble
         pv[i] = 16 * t + 4 * kq + i < kend ? __builtin_amdgcn_exp2f(z[4 * t + i] - m) : 0.0f;
         l += pv[i];
       }
-      *reinterpret_cast<uint2*>(&pw[hc][32 * wave + 8 * t + 2 * kq]) =
-          make_uint2(pack_bf16(pv[0], pv[1]), pack_bf16(pv[2], pv[3]));
+      float po[4];  // the weights four keys on (or before)
+#pragma unroll
+      for (int i = 0; i < 4; i++) po[i] = __shfl_xor(pv[i], 16, 64);
+      if ((kq & 1) == 0)
+        *reinterpret_cast<uint4*>(&pw[hc][32 * wave + 4 * (2 * t + (kq >> 1))]) =
+            make_uint4(pack_bf16(pv[0], po[0]), pack_bf16(pv[1], po[1]), pack_bf16(pv[2], po[2]),
+                       pack_bf16(pv[3], po[3]));
     }
     l += __shfl_xor(l, 16, 64);  // (the four lanes of a head take this branch together)
     l += __shfl_xor(l, 32, 64);
     if (kq == 0) red[wave][hc][1] = l;
   }
   __syncthreads();
-  // P V: wave w sums keys 64w .. 64w+63 for dims 2*lane, 2*lane+1, a key
-  // pair per dot2 (weights rounded once to bf16, fp32 accumulation); slots
-  // past the chunk end carry weight 0
-  float2 acc[GM];
+  // P V: a lane sums its keys of the wave's 64 for dims 8 hc .. + 7, a key pair per
+  // dot2 (weights rounded once to bf16, fp32 accumulation; slots past the chunk end
+  // carry weight 0); the four lanes of a dim group are added, kq order fixed.
+  // Four heads at a time share the value pairs.
+  for (int h0 = 0; h0 < GM; h0 += 4) {
+    if (h0 >= G) break;
+    constexpr int kH = GM < 4 ? GM : 4;
+    float acc[kH][8];
 #pragma unroll
-  for (int hl = 0; hl < GM; hl++) acc[hl] = make_float2(0.0f, 0.0f);
+    for (int e = 0; e < kH; e++)
 #pragma unroll
-  for (int e2 = 0; e2 < 32; e2++) {
-    const uint32_t v_lo = wv[2 * e2], v_hi = wv[2 * e2 + 1];
-    const uint32_t vx = __builtin_amdgcn_perm(v_hi, v_lo, 0x05040100u);  // dim 2*lane of both keys
-    const uint32_t vy = __builtin_amdgcn_perm(v_hi, v_lo, 0x07060302u);  // dim 2*lane+1
+      for (int d = 0; d < 8; d++) acc[e][d] = 0.0f;
 #pragma unroll
-    for (int hl = 0; hl < GM; hl++) {
-      if (hl < G) {
-        const bf16x2_t pp = as_bf16x2(pw[hl][32 * wave + e2]);
-        acc[hl].x = __builtin_amdgcn_fdot2_f32_bf16(pp, as_bf16x2(vx), acc[hl].x, false);
-        acc[hl].y = __builtin_amdgcn_fdot2_f32_bf16(pp, as_bf16x2(vy), acc[hl].y, false);
+    for (int j = 0; j < 8; j++) {
+      const uint32_t lo[4] = {wv[2 * j].x, wv[2 * j].y, wv[2 * j].z, wv[2 * j].w};
+      const uint32_t hi[4] = {wv[2 * j + 1].x, wv[2 * j + 1].y, wv[2 * j + 1].z, wv[2 * j + 1].w};
+      bf16x2_t vv[8];
+#pragma unroll
+      for (int c = 0; c < 4; c++) {
+        vv[2 * c] = as_bf16x2(__builtin_amdgcn_perm(hi[c], lo[c], 0x05040100u));
+        vv[2 * c + 1] = as_bf16x2(__builtin_amdgcn_perm(hi[c], lo[c], 0x07060302u));
+      }
+#pragma unroll
+      for (int e = 0; e < kH; e++) {
+        const bf16x2_t pp = as_bf16x2(pw[h0 + e][32 * wave + 4 * j + kq]);
+#pragma unroll
+        for (int d = 0; d < 8; d++)
+          acc[e][d] = __builtin_amdgcn_fdot2_f32_bf16(pp, vv[d], acc[e][d], false);
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < kH; e++) {
+#pragma unroll
+      for (int d = 0; d < 8; d++) {
+        acc[e][d] += __shfl_xor(acc[e][d], 16, 64);
+        acc[e][d] += __shfl_xor(acc[e][d], 32, 64);
+      }
+      if (kq == 0 && h0 + e < G) {
+        float4* dst = reinterpret_cast<float4*>(&accs[wave][h0 + e][4 * hc]);
+        dst[0] = make_float4(acc[e][0], acc[e][1], acc[e][2], acc[e][3]);
+        dst[1] = make_float4(acc[e][4], acc[e][5], acc[e][6], acc[e][7]);
       }
     }
   }
-#pragma unroll
-  for (int hl = 0; hl < GM; hl++)
-    if (hl < G) accs[wave][hl][lane] = acc[hl];
   __syncthreads();
   // normalised partial and lse per attending head; wave w handles heads w, w+4, ...
   for (int hl = wave; hl < G; hl += 4) {
