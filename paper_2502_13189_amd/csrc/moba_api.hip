@@ -811,8 +811,7 @@ moba_status moba_forward(const moba_tensor* q, const moba_tensor* k, const moba_
   { Phase ph("pool", stream);  // bf16: and the V^T pack
     MOBA_LAUNCH(in.bf16 ? launch_pool_pack(static_cast<const __hip_bfloat16*>(in.k.data), in.k.st,
                                            in.k.sh, static_cast<const __hip_bfloat16*>(in.v.data),
-                                           in.v.st, in.v.sh, d_seqs, p, true, kbar, fb.kterm, vt,
-                                           stream)
+                                           in.v.st, in.v.sh, d_seqs, p, kbar, fb.kterm, vt, stream)
                         : launch_pool(in.k.data, false, in.k.st, in.k.sh, d_seqs, p, kbar, nullptr,
                                       stream)); }
   { Phase ph("gate", stream);
@@ -1033,7 +1032,7 @@ moba_status backward_impl(const moba_tensor* q, const moba_tensor* k, const moba
   // the forward's selection and routing, recomputed
   { Phase ph("pool", stream);  // and the K^T pack
     const __hip_bfloat16* kp = static_cast<const __hip_bfloat16*>(in.k.data);
-    MOBA_LAUNCH(launch_pool_pack(kp, in.k.st, in.k.sh, kp, in.k.st, in.k.sh, d_seqs, p, true, b.kbar,
+    MOBA_LAUNCH(launch_pool_pack(kp, in.k.st, in.k.sh, kp, in.k.st, in.k.sh, d_seqs, p, b.kbar,
                                  b.kterm, b.kt, stream)); }
   { Phase ph("gate", stream);
     MOBA_LAUNCH(launch_gate(in.q.data, true, in.q.st, in.q.sh, b.kbar, b.kterm, d_seqs, p, b.sel,
@@ -1136,8 +1135,8 @@ moba_status dense_forward_impl(const Inputs& in, const View& vo, moba_tensor* ls
   a.g1 = p.Hkv;
   if (in.bf16) {
     Phase ph("vt_pack", stream);
-    MOBA_LAUNCH(launch_pool_pack(nullptr, 0, 0, static_cast<const __hip_bfloat16*>(in.v.data),
-                                 in.v.st, in.v.sh, d_seqs, p, false, nullptr, nullptr, vt, stream));
+    MOBA_LAUNCH(launch_pack(static_cast<const __hip_bfloat16*>(in.v.data), in.v.st, in.v.sh, d_seqs,
+                            p, vt, stream));
   }
   { Phase ph("dense", stream);
     MOBA_LAUNCH(in.bf16 ? launch_attn_causal_bf16(true, a, p, stream)

@@ -70,11 +70,14 @@ struct Problem {
 hipError_t launch_pool(const void* k, bool bf16, int64_t k_st, int64_t k_sh, const SeqInfo* seqs,
                        const Problem& p, float* kbar, __hip_bfloat16* kterm, hipStream_t st);
 
-// The packed tiles of v (bf16); with `pool`, k's block means too, in one launch.
+// k's block means and the packed tiles of v (bf16) in one launch.
 hipError_t launch_pool_pack(const __hip_bfloat16* k, int64_t k_st, int64_t k_sh,
                             const __hip_bfloat16* v, int64_t v_st, int64_t v_sh,
-                            const SeqInfo* seqs, const Problem& p, bool pool, float* kbar,
+                            const SeqInfo* seqs, const Problem& p, float* kbar,
                             __hip_bfloat16* kterm, __hip_bfloat16* vt, hipStream_t st);
+// The packed tiles alone.
+hipError_t launch_pack(const __hip_bfloat16* v, int64_t v_st, int64_t v_sh, const SeqInfo* seqs,
+                       const Problem& p, __hip_bfloat16* vt, hipStream_t st);
 
 // bf16 queries read kterm (from launch_pool), fp32 queries kbar.  gcount
 // (nullable): [Hkv, gate_groups, nblk_max], every group's kept past blocks.

@@ -54,7 +54,6 @@ struct Load8<float> {
 constexpr int kThreads = 1024;
 constexpr int kPoolRows = kThreads / 16;  // token rows a pool work-group reads at a time
 constexpr int kPoolAhead = 4;             // loads in flight per thread
-constexpr int kPackTiles = kThreads / 256;  // tiles per pack work-group, four waves each
 constexpr int kPackRow = 32 + 2;
 
 // kterm (nullable): the block keys split exactly into three bf16 planes,
@@ -178,7 +177,19 @@ __device__ __forceinline__ void pack_tile(const __hip_bfloat16* __restrict__ v, 
   }
 }
 
+// The pack by itself (dense attention): one tile per work-group (small dense calls ran 0.5-1.3 us
+// slower with 1024-thread ones).
+__global__ __launch_bounds__(256) void pack_kernel(const __hip_bfloat16* __restrict__ v,
+                                                   int64_t v_st, int64_t v_sh,
+                                                   const SeqInfo* __restrict__ seqs, Problem p,
+                                                   __hip_bfloat16* __restrict__ vt) {
+  __shared__ __attribute__((aligned(16))) uint16_t tile[4][kKeyTile][kPackRow];
+  const int wave = threadIdx.x >> 6;
+  pack_tile(v, v_st, v_sh, seqs, p, blockIdx.x, blockIdx.y, wave, vt, tile[wave]);
+}
+
 // Work-groups [0, npool): pool (block, kv-head); then pack (kPackTiles tiles, kv-head).
+constexpr int kPackTiles = kThreads / 256;  // tiles per pack work-group, four waves each
 template <typename T, bool PACK>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8)))
 void pool_pack_kernel(
@@ -222,12 +233,19 @@ hipError_t launch_pool(const void* k, bool bf16, int64_t k_st, int64_t k_sh, con
   return hipGetLastError();
 }
 
+hipError_t launch_pack(const __hip_bfloat16* v, int64_t v_st, int64_t v_sh, const SeqInfo* seqs,
+                       const Problem& p, __hip_bfloat16* vt, hipStream_t st) {
+  if (p.vt_tiles == 0) return hipSuccess;
+  pack_kernel<<<dim3((unsigned)p.vt_tiles, p.Hkv), 256, 0, st>>>(v, v_st, v_sh, seqs, p, vt);
+  return hipGetLastError();
+}
+
 hipError_t launch_pool_pack(const __hip_bfloat16* k, int64_t k_st, int64_t k_sh,
                             const __hip_bfloat16* v, int64_t v_st, int64_t v_sh,
-                            const SeqInfo* seqs, const Problem& p, bool pool, float* kbar,
+                            const SeqInfo* seqs, const Problem& p, float* kbar,
                             __hip_bfloat16* kterm, __hip_bfloat16* vt, hipStream_t st) {
   if (p.vt_tiles == 0) return hipSuccess;
-  const uint32_t npool = pool ? (uint32_t)p.nblk_total * (uint32_t)p.Hkv : 0;
+  const uint32_t npool = (uint32_t)p.nblk_total * (uint32_t)p.Hkv;
   const uint32_t npack = (uint32_t)((p.vt_tiles + kPackTiles - 1) / kPackTiles) * (uint32_t)p.Hkv;
   pool_pack_kernel<__hip_bfloat16, true><<<npool + npack, kThreads, 0, st>>>(
       k, k_st, k_sh, v, v_st, v_sh, seqs, p, npool, kbar, kterm, vt);
