@@ -90,7 +90,9 @@ __global__ __launch_bounds__(256) void bwd_delta_kernel(BwdArgs a, Problem p) {
 
 __global__ __launch_bounds__(256) void bwd_rec_kernel(BwdArgs a, Problem p) {
   const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (e >= p.hist_entries) return;
+  // the entries the routing wrote: fewer than planned where a row kept fewer blocks
+  // (one whose gate scores are not finite)
+  if (e >= a.bin_start[(int64_t)p.Hkv * p.nblk_total]) return;
   const uint64_t kh = (uint64_t)(p.topk - 1);
   const uint64_t TG = (uint64_t)p.T * p.G;
   const uint64_t r = (uint64_t)a.entries[e] / kh;

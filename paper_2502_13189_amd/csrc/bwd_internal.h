@@ -40,7 +40,7 @@ struct BwdArgs {
   const int32_t* bin_count;
   const uint32_t* entries;
   float2* ld;        // [Hq, T]: (lse * log2 e, Delta = <dO, O>)
-  int4* rec;         // [hist_entries]: (t, h, lse * log2 e, Delta) of each routed entry
+  int4* rec;         // [bin_start[nbins]]: (t, h, lse * log2 e, Delta) of each routed entry
   float* dq_part;    // [rows_chunk * (topk-1), D] fp32, scaled history-slot dQ
   const CausalTile* tiles;
   int64_t ntiles;
