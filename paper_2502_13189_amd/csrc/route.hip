@@ -29,9 +29,10 @@
 //              one by one.
 // Entry value: r * (topk - 1) + slot, where slot is the position of the block
 // in the row's ascending selection.  A history slot holding no past block of
-// its row (outside [0, c), which the gate never writes) is skipped by the
-// count and the scatter alike, so every LDS and global index stays within the
-// row's sequence.
+// its row (outside [0, c): a row whose gate scores are not finite has some, or
+// a caller's own selection) is skipped by the counts and every scatter alike, so
+// every LDS and global index stays within the row's sequence and the other rows'
+// entries keep their places.
 #include "moba_internal.h"
 
 namespace moba {
@@ -422,7 +423,10 @@ __global__ __launch_bounds__(kRouteRows) void route_scatter_scan_kernel(
   const int32_t* mine =
       sel + ((int64_t)(sq.tok_start + tl) * p.sel_st + (int64_t)g * p.sel_sg + hl) * p.topk;
 #pragma unroll
-  for (int x = 0; x < KH; x++) js[x] = x < nh ? mine[x] : -1;
+  for (int x = 0; x < KH; x++) {
+    const int j = x < nh ? mine[x] : -1;
+    js[x] = (unsigned)j < (unsigned)(tl / p.B) ? j : -1;  // as the gate counted them
+  }
 
   // this thread's bin: its total, and for the work-group's own sequence and
   // kv-head the entries of earlier chunks and of this one

@@ -63,3 +63,42 @@ def test_large_batch(kind):
     close(out, ref, ok)
     close(lse.T, rlse.T, ok)
     close(dq, rdq, ok)
+
+
+@pytest.mark.parametrize("seqlens,hq,hkv,B,topk,bad", [
+    ((1500,), 2, 2, 64, 3, [(300, 0), (301, 0), (200, 1)]),    # chunk of 1024 tokens: 16 blocks
+    ((600, 500), 8, 2, 64, 3, [(255, 5), (256, 0), (900, 7)]),  # 256 tokens, 4 blocks
+    ((700,), 6, 2, 16, 8, [(140, 1), (143, 1), (699, 5)]),     # groups of 3
+])
+@pytest.mark.parametrize("kind", ["nan", "-inf"])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_small_batch(seqlens, hq, hkv, B, topk, bad, kind, dtype):
+    """The gate's own counts and the scanning scatter: the other rows against the clean
+    run (fp32: bit for bit), and all of them bit for bit against the count and scan
+    kernels (the same batch with a filler sequence that brings it past 1024 bins)."""
+    T, fill = sum(seqlens), 1040 * B
+    q, qb, k, v, cu = bad_inputs(seqlens + (fill,), hq, hkv, B, bad, kind, dtype, T)
+    ok = other_rows(q[:T], bad)
+    cus = cu[:-1].contiguous()
+    ref, rlse = binding.forward(q[:T], k[:T], v[:T], cus, B, topk)
+    big, blse = binding.forward(qb, k, v, cu, B, topk)
+    out, lse = binding.forward(qb[:T], k[:T], v[:T], cus, B, topk)
+    assert torch.equal(out[ok], big[:T][ok]) and torch.equal(lse.T[ok], blse.T[:T][ok])
+    if dtype == torch.float32:
+        assert torch.equal(out[ok], ref[ok]) and torch.equal(lse.T[ok], rlse.T[ok])
+        return
+    close(out, ref, ok)
+    close(lse.T, rlse.T, ok)
+    dout = inputs.make_dout(q.shape, dtype, T, device=DEV)
+    rdq = binding.backward(q[:T], k[:T], v[:T], cus, B, topk, ref, rlse, dout[:T])[0]
+    bdq = binding.backward(qb, k, v, cu, B, topk, big, blse, dout)[0]
+    dq, dk, dv = binding.backward(qb[:T], k[:T], v[:T], cus, B, topk, out, lse, dout[:T])
+    assert torch.equal(dq[ok], bdq[:T][ok])
+    close(dq, rdq, ok)
+    # keys outside the bad rows' own blocks do not see them
+    reach = torch.ones((T, hkv), dtype=torch.bool, device=DEV)
+    for t, h in bad:
+        s0 = max(int(c) for c in cus if int(c) <= t)
+        b0 = s0 + (t - s0) // B * B
+        reach[b0:b0 + B, h // (hq // hkv)] = False
+    assert torch.isfinite(dk[reach].float()).all() and torch.isfinite(dv[reach].float()).all()
