@@ -121,7 +121,8 @@ __global__ __launch_bounds__(256) void decode_gate_kernel(DecodeArgs a, Problem 
       }
       const float p1 = __shfl_down(acc, 1, 4), p2 = __shfl_down(acc, 2, 4), p3 = __shfl_down(acc, 3, 4);
       const int j = j0 + 64 * e + (tid >> 2);
-      if (quarter == 0 && j < c) sc[j] = ((acc + p1) + p2) + p3;
+      // NaN counts as -inf, so that the order is total and exactly nh blocks are kept
+      if (quarter == 0 && j < c) sc[j] = fmaxf(((acc + p1) + p2) + p3, -INFINITY);
     }
   }
   if (tid < 4) sc[c + tid] = -INFINITY;  // the rank loop reads whole groups of four

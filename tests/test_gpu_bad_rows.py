@@ -1,6 +1,7 @@
-"""A query row whose gate scores are not finite (NaN, or all -inf) keeps no past block,
-so fewer selections are routed than planned.  Its own results are undefined; every
-other row's forward and dQ are the ones it has without the bad row."""
+"""A query row whose gate scores are not finite (NaN, or all -inf) keeps no past block
+in the prefill, so fewer selections are routed than planned.  Its own results are
+undefined; every other row's forward, dQ and decode are the ones it has without the
+bad row."""
 import pytest
 import torch
 
@@ -102,3 +103,32 @@ def test_small_batch(seqlens, hq, hkv, B, topk, bad, kind, dtype):
         b0 = s0 + (t - s0) // B * B
         reach[b0:b0 + B, h // (hq // hkv)] = False
     assert torch.isfinite(dk[reach].float()).all() and torch.isfinite(dv[reach].float()).all()
+
+
+@pytest.mark.parametrize("seqlens,hq,hkv,B,topk", [
+    ((3000, 700, 900), 4, 2, 16, 3),     # 187 blocks: selection by rank
+    ((20000, 300, 5000), 8, 2, 16, 5),   # 1249 blocks: by argmax rounds
+])
+@pytest.mark.parametrize("noalloc", [False, True])
+def test_decode(seqlens, hq, hkv, B, topk, noalloc):
+    """A bad row keeps as many blocks as any: more would overwrite other rows'
+    selections.  Every other (sequence, head) of the batch keeps its bits."""
+    q, k, v, cu = inputs.make(seqlens, hq, hkv, 128, torch.bfloat16, B, 0.5, 3, device=DEV)
+    qd = q[(cu[1:] - 1).to(torch.int64).to(DEV)].contiguous()
+    bad = [(0, 1), (1, hq - 1)]
+    qb = qd.clone()
+    for s, h in bad:
+        qb[s, h] = float("nan")
+    kbar = binding.pool(k, cu, B)
+
+    def run(x):
+        if not noalloc:
+            return binding.decode(x, k, v, cu, B, topk, kbar=kbar)
+        return binding.decode_noalloc(x, k, v, cu, B, topk, torch.empty_like(x),
+                                      torch.empty((hq, len(seqlens)), device=DEV), kbar=kbar)
+
+    ref, rlse = run(qd)
+    out, lse = run(qb)
+    ok = other_rows(qd, bad)
+    assert torch.equal(out[ok], ref[ok]) and torch.equal(lse.T[ok], rlse.T[ok])
+    assert torch.isnan(out[~ok].float()).all()
