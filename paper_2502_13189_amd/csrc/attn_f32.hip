@@ -50,9 +50,10 @@ __device__ __forceinline__ f32x16 mfma_f32(float a, float b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
 }
 
-// nhist: work-groups of history tiles (a multiple of 8), first in the grid.
+// nhist: work-groups of history tiles (a multiple of 8), first in the grid; first:
+// the first work-group of this piece of it.
 __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(2)))
-void attn_f32_kernel(AttnArgs a, Problem p, int64_t nhist) {
+void attn_f32_kernel(AttnArgs a, Problem p, uint32_t nhist, uint32_t first) {
   // the four waves' results; the query rows live in the first part until then
   __shared__ float4 lds[kWaves * kRowsWg * kQRow];
   __shared__ float sm[kWaves][kRowsWg], sl[kWaves][kRowsWg];
@@ -61,7 +62,8 @@ void attn_f32_kernel(AttnArgs a, Problem p, int64_t nhist) {
   const int qc = lane & 31, hh = lane >> 5;
 
   // ------------------------------------------------------------ tile setup
-  const bool hist = (int64_t)blockIdx.x < nhist;
+  const uint32_t bx = first + blockIdx.x;
+  const bool hist = bx < nhist;
   int g, h;
   int64_t kbeg, kend, dst, tmin;
   int t;  // (T is below 2^31)
@@ -72,9 +74,9 @@ void attn_f32_kernel(AttnArgs a, Problem p, int64_t nhist) {
     const int64_t tbeg = a.bin_tile_start[a.g0 * nb];
     const int64_t tend = a.bin_tile_start[a.g1 * nb];
     const uint32_t per = (uint32_t)((tend - tbeg) * kSubTiles + 7) / 8;
-    const uint32_t w = (blockIdx.x % 8) * per + blockIdx.x / 8;
+    const uint32_t w = (bx % 8) * per + bx / 8;
     const int64_t tile = tbeg + w / kSubTiles;
-    if (blockIdx.x / 8 >= per || tile >= tend) return;
+    if (bx / 8 >= per || tile >= tend) return;
     const int bin = a.tile_bin[tile];
     g = bin / p.nblk_total;
     const int b = bin % p.nblk_total;
@@ -98,7 +100,7 @@ void attn_f32_kernel(AttnArgs a, Problem p, int64_t nhist) {
   } else {
     // 8 consecutive tiles of the list sit on the 8 XCDs; the sub-tiles of a
     // tile follow on its XCD
-    const uint32_t x = blockIdx.x - (uint32_t)nhist;
+    const uint32_t x = bx - nhist;
     const uint32_t per = (uint32_t)((a.ntiles + 7) / 8 * 8 * kSubTiles);
     g = a.g0 + (int)(x / per);
     const uint32_t y = x % per;
@@ -271,9 +273,9 @@ hipError_t launch_attn_f32(const AttnArgs& a, const Problem& p, int64_t hist_til
   if (a.g1 <= a.g0) return hipSuccess;
   const int64_t nhist = (hist_tiles * kSubTiles + 7) / 8 * 8;
   const int64_t ncur = (a.ntiles + 7) / 8 * 8 * kSubTiles * (a.g1 - a.g0);
-  if (nhist + ncur <= 0) return hipSuccess;
-  attn_f32_kernel<<<(unsigned)(nhist + ncur), 64 * kWaves, 0, st>>>(a, p, nhist);
-  return hipGetLastError();
+  return launch_pieces(nhist + ncur, 64 * kWaves, [&](uint32_t first, unsigned n) {
+    attn_f32_kernel<<<n, 64 * kWaves, 0, st>>>(a, p, (uint32_t)nhist, first);
+  });
 }
 
 }  // namespace moba

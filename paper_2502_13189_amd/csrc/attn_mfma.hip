@@ -162,14 +162,16 @@ __device__ __forceinline__ void store_staged(__hip_bfloat16* base, const u32x4* 
 
 // NW waves: 32 NW query rows per work-group, kRows / (32 NW) work-groups per
 // plan tile.  ncur: work-groups of causal tiles, first in a joint grid (a
-// multiple of 8; the longest tiles start early).
+// multiple of 8; the longest tiles start early); first: the first work-group of
+// this piece of a joint grid.
 // SKIP: waves pass over key tiles past their last row.  Only work-groups over more
 // than 64 tokens (G < NW / 2 heads per kv-head) have such waves; elsewhere the branch
 // around a tile's products would only cost (1.2% of the dense kernel at 16K tokens, 32/8
 // heads).
 template <int MODE, int NW, bool SKIP>
 __global__ __launch_bounds__(64 * NW, 8 / NW)
-void attn_mfma_kernel(AttnArgs a, Problem p, uint32_t ncur, const SeqInfo* __restrict__ seqs,
+void attn_mfma_kernel(AttnArgs a, Problem p, uint32_t ncur, uint32_t first,
+                      const SeqInfo* __restrict__ seqs,
                       const int32_t* __restrict__ tile_bin,
                       const int64_t* __restrict__ bin_start,
                       const int32_t* __restrict__ bin_tile_start,
@@ -183,7 +185,8 @@ void attn_mfma_kernel(AttnArgs a, Problem p, uint32_t ncur, const SeqInfo* __res
   const int qc = lane & 31, hh = lane >> 5;
 
   // ------------------------------------------------------------ tile setup
-  const bool hist = MODE == kHist || (MODE == kJoint && blockIdx.x >= ncur);
+  const uint32_t bx = MODE == kJoint ? first + blockIdx.x : blockIdx.x;
+  const bool hist = MODE == kHist || (MODE == kJoint && bx >= ncur);
   int g, s;
   int64_t kbeg, kend, tmin;
   int wlast = INT_MAX;  // last local token of this wave's rows (its last key)
@@ -196,7 +199,7 @@ void attn_mfma_kernel(AttnArgs a, Problem p, uint32_t ncur, const SeqInfo* __res
     // XCD-aware order: work-groups go round-robin to the 8 XCDs, so give each
     // XCD a contiguous run of tiles (tiles of one bin share its K/V block).
     const uint32_t per = MODE == kHist ? gridDim.x / 8 : ((uint32_t)(tend - tbeg) * kSubTiles + 7) / 8;
-    const uint32_t x = MODE == kHist ? blockIdx.x : blockIdx.x - ncur;
+    const uint32_t x = MODE == kHist ? bx : bx - ncur;
     const uint32_t w = (x % 8) * per + x / 8;
     const int64_t tile = tbeg + w / kSubTiles;
     if (x / 8 >= per || tile >= tend) return;
@@ -222,14 +225,14 @@ void attn_mfma_kernel(AttnArgs a, Problem p, uint32_t ncur, const SeqInfo* __res
     ri.h = g * p.G + (ok ? (int)((uint32_t)rem % (uint32_t)p.G) : 0);
     ri.dst = (int64_t)(ev - (uint64_t)a.g0 * TG * kh);
   } else {
-    int y = blockIdx.x, r0 = 0;
+    int y = (int)bx, r0 = 0;
     g = a.g0 + blockIdx.y;
     if constexpr (MODE == kJoint) {
       // groups of 8 consecutive tiles of the list sit on the 8 XCDs; the
       // work-groups of a tile follow each other on its XCD
       const uint32_t per = (uint32_t)a.ntiles * kSubTiles;
-      g = a.g0 + (int)(blockIdx.x / per);
-      const uint32_t z = blockIdx.x % per;
+      g = a.g0 + (int)(bx / per);
+      const uint32_t z = bx % per;
       y = (int)(z / (8 * kSubTiles) * 8 + z % 8);
       r0 = (int)(z / 8 % kSubTiles) * kRowsWg;
     }
@@ -357,11 +360,13 @@ namespace {
 
 template <int MODE, int NW>
 void launch_mode(dim3 grid, bool skip, const AttnArgs& a, const Problem& p, uint32_t ncur,
-                 hipStream_t st) {
+                 uint32_t first, hipStream_t st) {
   if (skip)
-    attn_mfma_kernel<MODE, NW, true><<<grid, 64 * NW, 0, st>>>(a, p, ncur, MOBA_ATTN_TABLES(a));
+    attn_mfma_kernel<MODE, NW, true><<<grid, 64 * NW, 0, st>>>(a, p, ncur, first,
+                                                               MOBA_ATTN_TABLES(a));
   else
-    attn_mfma_kernel<MODE, NW, false><<<grid, 64 * NW, 0, st>>>(a, p, ncur, MOBA_ATTN_TABLES(a));
+    attn_mfma_kernel<MODE, NW, false><<<grid, 64 * NW, 0, st>>>(a, p, ncur, first,
+                                                                MOBA_ATTN_TABLES(a));
 }
 
 }  // namespace
@@ -369,15 +374,15 @@ void launch_mode(dim3 grid, bool skip, const AttnArgs& a, const Problem& p, uint
 hipError_t launch_attn_hist_bf16(const AttnArgs& a, const Problem& p, int64_t tiles, hipStream_t st) {
   if (tiles <= 0) return hipSuccess;
   const int64_t grid = (tiles + 7) / 8 * 8;
-  attn_mfma_kernel<kHist, 8, false><<<(unsigned)grid, 512, 0, st>>>(a, p, 0, MOBA_ATTN_TABLES(a));
+  attn_mfma_kernel<kHist, 8, false><<<(unsigned)grid, 512, 0, st>>>(a, p, 0, 0, MOBA_ATTN_TABLES(a));
   return hipGetLastError();
 }
 
 hipError_t launch_attn_causal_bf16(bool dense, const AttnArgs& a, const Problem& p, hipStream_t st) {
   if (a.ntiles <= 0 || a.g1 <= a.g0) return hipSuccess;
   dim3 grid((unsigned)a.ntiles, a.g1 - a.g0);
-  if (dense) launch_mode<kDense, 8>(grid, p.G < 4, a, p, 0, st);
-  else launch_mode<kCur, 8>(grid, p.G < 4, a, p, 0, st);
+  if (dense) launch_mode<kDense, 8>(grid, p.G < 4, a, p, 0, 0, st);
+  else launch_mode<kCur, 8>(grid, p.G < 4, a, p, 0, 0, st);
   return hipGetLastError();
 }
 
@@ -388,8 +393,9 @@ hipError_t launch_attn_joint_bf16(const AttnArgs& a, const Problem& p, int64_t h
   if (a.ntiles <= 0 || a.g1 <= a.g0) return hipSuccess;
   const int64_t ncur = a.ntiles * 2 * (a.g1 - a.g0);
   const int64_t nhist = (hist_tiles * 2 + 7) / 8 * 8;
-  launch_mode<kJoint, 4>(dim3((unsigned)(ncur + nhist)), p.G < 2, a, p, (uint32_t)ncur, st);
-  return hipGetLastError();
+  return launch_pieces(ncur + nhist, 256, [&](uint32_t first, unsigned n) {
+    launch_mode<kJoint, 4>(dim3(n), p.G < 2, a, p, (uint32_t)ncur, first, st);
+  });
 }
 
 }  // namespace moba

@@ -55,7 +55,7 @@ __device__ __forceinline__ uint4 pack(const float (&f)[4], float inv) {
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void merge_kernel(AttnArgs a, Problem p) {
+__global__ __launch_bounds__(256) void merge_kernel(AttnArgs a, Problem p, uint32_t first) {
   constexpr int kDims = 16 / sizeof(T);  // dims per lane
   constexpr int kLanesPerRow = kHeadDim / kDims;
   constexpr int kRowsPerGroup = 256 / kLanesPerRow;
@@ -63,7 +63,7 @@ __global__ __launch_bounds__(256) void merge_kernel(AttnArgs a, Problem p) {
   const int64_t nrow = (int64_t)(a.g1 - a.g0) * TG;
   // r = (g - g0) * T * G + t * G + hl: the chunk-relative row, which is also
   // the row index of the history partials
-  const int64_t r = (int64_t)blockIdx.x * kRowsPerGroup + (threadIdx.x / kLanesPerRow);
+  const int64_t r = (int64_t)(first + blockIdx.x) * kRowsPerGroup + (threadIdx.x / kLanesPerRow);
   const int lr = threadIdx.x % kLanesPerRow;
   if (r >= nrow) return;
   const int gl = (int)(r / TG);
@@ -131,10 +131,10 @@ hipError_t launch_merge(bool bf16, const AttnArgs& a, const Problem& p, hipStrea
   const int64_t nrow = (int64_t)(a.g1 - a.g0) * p.T * p.G;
   if (nrow <= 0 || p.topk <= 1) return hipSuccess;
   const int64_t rows_wg = bf16 ? 16 : 8;
-  const unsigned grid = (unsigned)((nrow + rows_wg - 1) / rows_wg);
-  if (bf16) merge_kernel<__hip_bfloat16><<<grid, 256, 0, st>>>(a, p);
-  else merge_kernel<float><<<grid, 256, 0, st>>>(a, p);
-  return hipGetLastError();
+  return launch_pieces((nrow + rows_wg - 1) / rows_wg, 256, [&](uint32_t first, unsigned n) {
+    if (bf16) merge_kernel<__hip_bfloat16><<<n, 256, 0, st>>>(a, p, first);
+    else merge_kernel<float><<<n, 256, 0, st>>>(a, p, first);
+  });
 }
 
 }  // namespace moba

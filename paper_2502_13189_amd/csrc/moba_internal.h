@@ -64,6 +64,22 @@ struct Problem {
 };
 
 // ---------------------------------------------------------------- launches
+// HIP refuses a launch of 2^32 or more work items along x.  Batches of very many
+// short blocks pass that, so launches over (block, kv-head) pairs go through here:
+// launch(first, n) enqueues work-groups first .. first + n - 1 of `groups`, each
+// piece a multiple of 64 work-groups but the last (the kernels' maps to the 8 XCDs hold).
+template <typename F>
+hipError_t launch_pieces(int64_t groups, int threads, F launch) {
+  if (groups >= (int64_t(1) << 32)) return hipErrorInvalidConfiguration;  // (the index's type)
+  const int64_t most = ((int64_t(1) << 32) / threads - 1) / 64 * 64;
+  for (int64_t first = 0; first < groups; first += most) {
+    launch((uint32_t)first, (unsigned)(groups - first < most ? groups - first : most));
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 // Every launcher enqueues on `st` and returns the launch status.
 // kterm (nullable): also the three exact bf16 planes of kbar (hi, mid, lo;
 // each [nblk_total, Hkv, D]) that the bf16 gate reads.

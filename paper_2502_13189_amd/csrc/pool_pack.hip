@@ -189,25 +189,27 @@ __global__ __launch_bounds__(256) void pack_kernel(const __hip_bfloat16* __restr
 }
 
 // Work-groups [0, npool): pool (block, kv-head); then pack (kPackTiles tiles, kv-head).
+// first: this launch's first work-group.
 constexpr int kPackTiles = kThreads / 256;  // tiles per pack work-group, four waves each
 template <typename T, bool PACK>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8)))
 void pool_pack_kernel(
     const T* __restrict__ k, int64_t k_st, int64_t k_sh, const __hip_bfloat16* __restrict__ v,
-    int64_t v_st, int64_t v_sh, const SeqInfo* __restrict__ seqs, Problem p, uint32_t npool,
-    float* __restrict__ kbar, __hip_bfloat16* __restrict__ kterm, __hip_bfloat16* __restrict__ vt) {
+    int64_t v_st, int64_t v_sh, const SeqInfo* __restrict__ seqs, Problem p, uint32_t first,
+    uint32_t npool, float* __restrict__ kbar, __hip_bfloat16* __restrict__ kterm, __hip_bfloat16* __restrict__ vt) {
   constexpr size_t kPoolLds = sizeof(double) * (kThreads / 64) * kHeadDim;
   constexpr size_t kPackLds = sizeof(uint16_t) * (kThreads / 64) * kKeyTile * kPackRow;
   __shared__ __attribute__((aligned(16))) char lds[PACK && kPackLds > kPoolLds ? kPackLds : kPoolLds];
-  if (blockIdx.x < npool) {
-    pool_block<T>(k, k_st, k_sh, seqs, p, (int)(blockIdx.x % (uint32_t)p.nblk_total),
-                  (int)(blockIdx.x / (uint32_t)p.nblk_total), kbar, kterm,
+  const uint32_t x = first + blockIdx.x;
+  if (x < npool) {
+    pool_block<T>(k, k_st, k_sh, seqs, p, (int)(x % (uint32_t)p.nblk_total),
+                  (int)(x / (uint32_t)p.nblk_total), kbar, kterm,
                   reinterpret_cast<double(*)[kHeadDim]>(lds));
     return;
   }
   if constexpr (PACK) {
     const uint32_t per = (uint32_t)((p.vt_tiles + kPackTiles - 1) / kPackTiles);
-    const uint32_t y = blockIdx.x - npool;
+    const uint32_t y = x - npool;
     const int wave = threadIdx.x >> 6;
     const int64_t idx = (int64_t)(y % per) * kPackTiles + (wave >> 2);
     if (idx < p.vt_tiles)
@@ -221,16 +223,17 @@ void pool_pack_kernel(
 hipError_t launch_pool(const void* k, bool bf16, int64_t k_st, int64_t k_sh, const SeqInfo* seqs,
                        const Problem& p, float* kbar, __hip_bfloat16* kterm, hipStream_t st) {
   if (p.nblk_total == 0) return hipSuccess;
-  const uint32_t npool = (uint32_t)p.nblk_total * (uint32_t)p.Hkv;
-  if (bf16)
-    pool_pack_kernel<__hip_bfloat16, false><<<npool, kThreads, 0, st>>>(
-        static_cast<const __hip_bfloat16*>(k), k_st, k_sh, nullptr, 0, 0, seqs, p, npool, kbar,
-        kterm, nullptr);
-  else
-    pool_pack_kernel<float, false><<<npool, kThreads, 0, st>>>(
-        static_cast<const float*>(k), k_st, k_sh, nullptr, 0, 0, seqs, p, npool, kbar, kterm,
-        nullptr);
-  return hipGetLastError();
+  const int64_t npool = (int64_t)p.nblk_total * p.Hkv;
+  return launch_pieces(npool, kThreads, [&](uint32_t first, unsigned n) {
+    if (bf16)
+      pool_pack_kernel<__hip_bfloat16, false><<<n, kThreads, 0, st>>>(
+          static_cast<const __hip_bfloat16*>(k), k_st, k_sh, nullptr, 0, 0, seqs, p, first,
+          (uint32_t)npool, kbar, kterm, nullptr);
+    else
+      pool_pack_kernel<float, false><<<n, kThreads, 0, st>>>(
+          static_cast<const float*>(k), k_st, k_sh, nullptr, 0, 0, seqs, p, first, (uint32_t)npool,
+          kbar, kterm, nullptr);
+  });
 }
 
 hipError_t launch_pack(const __hip_bfloat16* v, int64_t v_st, int64_t v_sh, const SeqInfo* seqs,
@@ -245,11 +248,12 @@ hipError_t launch_pool_pack(const __hip_bfloat16* k, int64_t k_st, int64_t k_sh,
                             const SeqInfo* seqs, const Problem& p, float* kbar,
                             __hip_bfloat16* kterm, __hip_bfloat16* vt, hipStream_t st) {
   if (p.vt_tiles == 0) return hipSuccess;
-  const uint32_t npool = (uint32_t)p.nblk_total * (uint32_t)p.Hkv;
-  const uint32_t npack = (uint32_t)((p.vt_tiles + kPackTiles - 1) / kPackTiles) * (uint32_t)p.Hkv;
-  pool_pack_kernel<__hip_bfloat16, true><<<npool + npack, kThreads, 0, st>>>(
-      k, k_st, k_sh, v, v_st, v_sh, seqs, p, npool, kbar, kterm, vt);
-  return hipGetLastError();
+  const int64_t npool = (int64_t)p.nblk_total * p.Hkv;
+  const int64_t npack = (p.vt_tiles + kPackTiles - 1) / kPackTiles * p.Hkv;
+  return launch_pieces(npool + npack, kThreads, [&](uint32_t first, unsigned n) {
+    pool_pack_kernel<__hip_bfloat16, true><<<n, kThreads, 0, st>>>(
+        k, k_st, k_sh, v, v_st, v_sh, seqs, p, first, (uint32_t)npool, kbar, kterm, vt);
+  });
 }
 
 }  // namespace moba
