@@ -20,7 +20,8 @@
  *
  *   q    [T, Hq,  D]  bf16 or f32; last dim contiguous, any token/head stride
  *   k, v [T, Hkv, D]  same dtype as q; last dim contiguous
- *   out  [T, Hq,  D]  same dtype as q; last dim contiguous
+ *   out  [T, Hq,  D]  same dtype as q; last dim contiguous; may be q's own memory
+ *                      (with q's strides)
  *   lse  [Hq, T]      f32, contiguous; natural-log log-sum-exp of the scaled
  *                      logits over the keys each query attended
  *   cu_seqlens [S+1]  int32, contiguous, host OR device memory: cu[0] = 0,

@@ -269,13 +269,19 @@ void attn_f32_kernel(AttnArgs a, Problem p, uint32_t nhist, uint32_t first) {
 
 }  // namespace
 
-hipError_t launch_attn_f32(const AttnArgs& a, const Problem& p, int64_t hist_tiles, hipStream_t st) {
+hipError_t launch_attn_f32(const AttnArgs& a, const Problem& p, int64_t hist_tiles, bool in_place,
+                           hipStream_t st) {
   if (a.g1 <= a.g0) return hipSuccess;
   const int64_t nhist = (hist_tiles * kSubTiles + 7) / 8 * 8;
   const int64_t ncur = (a.ntiles + 7) / 8 * 8 * kSubTiles * (a.g1 - a.g0);
-  return launch_pieces(nhist + ncur, 64 * kWaves, [&](uint32_t first, unsigned n) {
-    attn_f32_kernel<<<n, 64 * kWaves, 0, st>>>(a, p, (uint32_t)nhist, first);
-  });
+  const auto run = [&](int64_t begin, int64_t groups) {
+    return launch_pieces(groups, 64 * kWaves, [&](uint32_t first, unsigned n) {
+      attn_f32_kernel<<<n, 64 * kWaves, 0, st>>>(a, p, (uint32_t)nhist, (uint32_t)begin + first);
+    });
+  };
+  if (!in_place) return run(0, nhist + ncur);
+  const hipError_t e = run(0, nhist);
+  return e != hipSuccess ? e : run(nhist, ncur);
 }
 
 }  // namespace moba

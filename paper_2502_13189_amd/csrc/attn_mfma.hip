@@ -389,13 +389,18 @@ hipError_t launch_attn_causal_bf16(bool dense, const AttnArgs& a, const Problem&
 bool attn_bf16_joint(const Problem& p) { return p.B <= kJointMaxBlock; }
 
 hipError_t launch_attn_joint_bf16(const AttnArgs& a, const Problem& p, int64_t hist_tiles,
-                                  hipStream_t st) {
+                                  bool in_place, hipStream_t st) {
   if (a.ntiles <= 0 || a.g1 <= a.g0) return hipSuccess;
   const int64_t ncur = a.ntiles * 2 * (a.g1 - a.g0);
   const int64_t nhist = (hist_tiles * 2 + 7) / 8 * 8;
-  return launch_pieces(ncur + nhist, 256, [&](uint32_t first, unsigned n) {
-    launch_mode<kJoint, 4>(dim3(n), p.G < 2, a, p, (uint32_t)ncur, first, st);
-  });
+  const auto run = [&](int64_t begin, int64_t groups) {
+    return launch_pieces(groups, 256, [&](uint32_t first, unsigned n) {
+      launch_mode<kJoint, 4>(dim3(n), p.G < 2, a, p, (uint32_t)ncur, (uint32_t)begin + first, st);
+    });
+  };
+  if (!in_place) return run(0, ncur + nhist);
+  const hipError_t e = run(ncur, nhist);
+  return e != hipSuccess ? e : run(0, ncur);
 }
 
 }  // namespace moba

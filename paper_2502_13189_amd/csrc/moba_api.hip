@@ -137,6 +137,18 @@ moba_status check_contig(const moba_tensor* t, int dtype, int ndim, const int64_
   return MOBA_OK;
 }
 
+// Whether two [T, H, D] views of elements of `el` bytes may share memory.  Views of
+// one wider buffer (equal token strides) share none if their heads lie apart in it.
+bool share_memory(const View& a, const View& b, int64_t T, int64_t el) {
+  const int64_t wa = (a.H - 1) * a.sh + kHeadDim, wb = (b.H - 1) * b.sh + kHeadDim;
+  const int64_t ia = (int64_t)(reinterpret_cast<uintptr_t>(a.data) / el);
+  const int64_t ib = (int64_t)(reinterpret_cast<uintptr_t>(b.data) / el);
+  if (ia + (T - 1) * a.st + wa <= ib || ib + (T - 1) * b.st + wb <= ia) return false;
+  if (a.st != b.st || wa > a.st || wb > a.st) return true;
+  const int64_t d = ((ib - ia) % a.st + a.st) % a.st;  // b's heads from a's, within a token
+  return d < wa || a.st - d < wb;
+}
+
 // Descriptor-level checks of cu_seqlens (no data access).
 moba_status check_cu_desc(const moba_tensor* cu) {
   if (!cu || !cu->data) return MOBA_ERR_NULL;
@@ -807,6 +819,7 @@ moba_status moba_forward(const moba_tensor* q, const moba_tensor* k, const moba_
   a.entries = rb.entries;
   a.tiles = d_tiles;
   a.ntiles = (int64_t)pl->tiles.size();
+  const bool in_place = share_memory(in.q, vo, p.T, in.bf16 ? 2 : 4);
 
   { Phase ph("pool", stream);  // bf16: and the V^T pack
     MOBA_LAUNCH(in.bf16 ? launch_pool_pack(static_cast<const __hip_bfloat16*>(in.k.data), in.k.st,
@@ -831,8 +844,8 @@ moba_status moba_forward(const moba_tensor* q, const moba_tensor* k, const moba_
             : 0;
     if (!in.bf16 || attn_bf16_joint(p)) {
       Phase ph("attn_hist", stream);  // and the current-block tiles
-      MOBA_LAUNCH(in.bf16 ? launch_attn_joint_bf16(a, p, hist_tiles, stream)
-                          : launch_attn_f32(a, p, hist_tiles, stream));
+      MOBA_LAUNCH(in.bf16 ? launch_attn_joint_bf16(a, p, hist_tiles, in_place, stream)
+                          : launch_attn_f32(a, p, hist_tiles, in_place, stream));
     } else {
       if (hist_tiles > 0) {
         Phase ph("attn_hist", stream);
@@ -1140,7 +1153,7 @@ moba_status dense_forward_impl(const Inputs& in, const View& vo, moba_tensor* ls
   }
   { Phase ph("dense", stream);
     MOBA_LAUNCH(in.bf16 ? launch_attn_causal_bf16(true, a, p, stream)
-                        : launch_attn_f32(a, p, 0, stream)); }
+                        : launch_attn_f32(a, p, 0, false, stream)); }
   return MOBA_OK;
 }
 

@@ -154,13 +154,16 @@ struct AttnArgs {
 // (extra work-groups exit).  Causal tiles: a.ntiles x (g1 - g0) work-groups.
 hipError_t launch_attn_hist_bf16(const AttnArgs& a, const Problem& p, int64_t grid, hipStream_t st);
 hipError_t launch_attn_causal_bf16(bool dense, const AttnArgs& a, const Problem& p, hipStream_t st);
-// bf16, where attn_bf16_joint(p): history and causal tiles in one launch.
+// bf16, where attn_bf16_joint(p): history and causal tiles in one launch; with
+// in_place (out shares memory with q) the history's, which read any row of q, in one
+// before the causal ones, which read the rows they write.
 bool attn_bf16_joint(const Problem& p);
 hipError_t launch_attn_joint_bf16(const AttnArgs& a, const Problem& p, int64_t hist_tiles,
-                                  hipStream_t st);
+                                  bool in_place, hipStream_t st);
 // fp32: the chunk's history tiles (at most hist_tiles, 0: none) and its causal
-// tiles in one launch.
-hipError_t launch_attn_f32(const AttnArgs& a, const Problem& p, int64_t hist_tiles, hipStream_t st);
+// tiles, in the same way.
+hipError_t launch_attn_f32(const AttnArgs& a, const Problem& p, int64_t hist_tiles, bool in_place,
+                           hipStream_t st);
 // Folds the history partials of chunk rows into out / lse in place.
 hipError_t launch_merge(bool bf16, const AttnArgs& a, const Problem& p, hipStream_t st);
 
