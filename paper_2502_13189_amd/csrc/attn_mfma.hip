@@ -47,7 +47,6 @@
 // partials into the current-block result).
 #include "mfma_tile.h"
 
-#include <limits.h>
 #include <math.h>
 
 namespace moba {
@@ -164,11 +163,10 @@ __device__ __forceinline__ void store_staged(__hip_bfloat16* base, const u32x4* 
 // plan tile.  ncur: work-groups of causal tiles, first in a joint grid (a
 // multiple of 8; the longest tiles start early); first: the first work-group of
 // this piece of a joint grid.
-// SKIP: waves pass over key tiles past their last row.  Only work-groups over more
-// than 64 tokens (G < NW / 2 heads per kv-head) have such waves; elsewhere the branch
-// around a tile's products would only cost (1.2% of the dense kernel at 16K tokens, 32/8
-// heads).
-template <int MODE, int NW, bool SKIP>
+// (Waves do not pass over key tiles past their last row: the work-group's other waves
+// need them and the barrier holds all.  A branch for it cost 1-3% of the dense kernel at 1K-16K
+// tokens and 1-4 heads per kv-head, 0-2% of the others, and gained nowhere.)
+template <int MODE, int NW>
 __global__ __launch_bounds__(64 * NW, 8 / NW)
 void attn_mfma_kernel(AttnArgs a, Problem p, uint32_t ncur, uint32_t first,
                       const SeqInfo* __restrict__ seqs,
@@ -189,7 +187,6 @@ void attn_mfma_kernel(AttnArgs a, Problem p, uint32_t ncur, uint32_t first,
   const bool hist = MODE == kHist || (MODE == kJoint && bx >= ncur);
   int g, s;
   int64_t kbeg, kend, tmin;
-  int wlast = INT_MAX;  // last local token of this wave's rows (its last key)
   RowInfo ri;
   const int rloc = wave * 32 + qc;  // this lane's query row within the work-group
   if (hist) {
@@ -248,7 +245,6 @@ void attn_mfma_kernel(AttnArgs a, Problem p, uint32_t ncur, uint32_t first,
     ri.t = ct.t0 + rr / p.G;
     ri.h = g * p.G + rr % p.G;
     ri.dst = 0;
-    wlast = ct.t0 + (r0 + min(32 * wave + 31, nrow - 1)) / p.G;
   }
   // the tile's key range is wave-uniform: keep it in scalar registers
   g = __builtin_amdgcn_readfirstlane(g);
@@ -258,9 +254,6 @@ void attn_mfma_kernel(AttnArgs a, Problem p, uint32_t ncur, uint32_t first,
   tmin = uniform64(tmin);
   const SeqInfo sq = seqs[s];
   const int64_t tok0 = sq.tok_start;
-  // key tiles past the wave's last row hold no key for it
-  const int ilast = hist ? INT_MAX
-                         : __builtin_amdgcn_readfirstlane((wlast - (int)tok0) / kKeyTile);
 
   // ---------------------------------------------------------- Q^T operands
   bf16x8 qf[8];
@@ -313,20 +306,18 @@ void attn_mfma_kernel(AttnArgs a, Problem p, uint32_t ncur, uint32_t first,
       dma_k(D, i + 1, lds + (cur ^ 1) * kBufK);
       dma_v(D, i + 1, lds + 2 * kBufK + (cur ^ 1) * kBufV);
     }
-    if (!SKIP || i <= ilast) {
-      qk(sc, lds + cur * kBufK, ro, qf);
-      const int64_t u0 = tok0 + (int64_t)i * kKeyTile;
-      const bool edge =
-          u0 < kbeg || u0 + kKeyTile > kend || (MODE != kHist && u0 + kKeyTile - 1 > tmin);
-      int lo = 0, hi = kKeyTile;
-      if (edge) {
-        lo = (int)max((int64_t)0, kbeg - u0) - 4 * hh;
-        const int64_t lim = min((int64_t)kKeyTile, kend - u0);
-        hi = (int)(hist ? lim : min(lim, ri.t + 1 - u0)) - 4 * hh;
-      }
-      softmax<MODE>(sc, m, l, o, pb, edge, lo, hi, c2);
-      pv(o, lds + 2 * kBufK + cur * kBufV, ro, pb);
+    qk(sc, lds + cur * kBufK, ro, qf);
+    const int64_t u0 = tok0 + (int64_t)i * kKeyTile;
+    const bool edge =
+        u0 < kbeg || u0 + kKeyTile > kend || (MODE != kHist && u0 + kKeyTile - 1 > tmin);
+    int lo = 0, hi = kKeyTile;
+    if (edge) {
+      lo = (int)max((int64_t)0, kbeg - u0) - 4 * hh;
+      const int64_t lim = min((int64_t)kKeyTile, kend - u0);
+      hi = (int)(hist ? lim : min(lim, ri.t + 1 - u0)) - 4 * hh;
     }
+    softmax<MODE>(sc, m, l, o, pb, edge, lo, hi, c2);
+    pv(o, lds + 2 * kBufK + cur * kBufV, ro, pb);
     dma_wait();
     __syncthreads();
   }
@@ -356,33 +347,18 @@ void attn_mfma_kernel(AttnArgs a, Problem p, uint32_t ncur, uint32_t first,
 #define MOBA_ATTN_TABLES(a) \
   (a).seqs, (a).tile_bin, (a).bin_start, (a).bin_tile_start, (a).bin_count, (a).entries, (a).tiles
 
-namespace {
-
-template <int MODE, int NW>
-void launch_mode(dim3 grid, bool skip, const AttnArgs& a, const Problem& p, uint32_t ncur,
-                 uint32_t first, hipStream_t st) {
-  if (skip)
-    attn_mfma_kernel<MODE, NW, true><<<grid, 64 * NW, 0, st>>>(a, p, ncur, first,
-                                                               MOBA_ATTN_TABLES(a));
-  else
-    attn_mfma_kernel<MODE, NW, false><<<grid, 64 * NW, 0, st>>>(a, p, ncur, first,
-                                                                MOBA_ATTN_TABLES(a));
-}
-
-}  // namespace
-
 hipError_t launch_attn_hist_bf16(const AttnArgs& a, const Problem& p, int64_t tiles, hipStream_t st) {
   if (tiles <= 0) return hipSuccess;
   const int64_t grid = (tiles + 7) / 8 * 8;
-  attn_mfma_kernel<kHist, 8, false><<<(unsigned)grid, 512, 0, st>>>(a, p, 0, 0, MOBA_ATTN_TABLES(a));
+  attn_mfma_kernel<kHist, 8><<<(unsigned)grid, 512, 0, st>>>(a, p, 0, 0, MOBA_ATTN_TABLES(a));
   return hipGetLastError();
 }
 
 hipError_t launch_attn_causal_bf16(bool dense, const AttnArgs& a, const Problem& p, hipStream_t st) {
   if (a.ntiles <= 0 || a.g1 <= a.g0) return hipSuccess;
   dim3 grid((unsigned)a.ntiles, a.g1 - a.g0);
-  if (dense) launch_mode<kDense, 8>(grid, p.G < 4, a, p, 0, 0, st);
-  else launch_mode<kCur, 8>(grid, p.G < 4, a, p, 0, 0, st);
+  if (dense) attn_mfma_kernel<kDense, 8><<<grid, 512, 0, st>>>(a, p, 0, 0, MOBA_ATTN_TABLES(a));
+  else attn_mfma_kernel<kCur, 8><<<grid, 512, 0, st>>>(a, p, 0, 0, MOBA_ATTN_TABLES(a));
   return hipGetLastError();
 }
 
@@ -395,7 +371,8 @@ hipError_t launch_attn_joint_bf16(const AttnArgs& a, const Problem& p, int64_t h
   const int64_t nhist = (hist_tiles * 2 + 7) / 8 * 8;
   const auto run = [&](int64_t begin, int64_t groups) {
     return launch_pieces(groups, 256, [&](uint32_t first, unsigned n) {
-      launch_mode<kJoint, 4>(dim3(n), p.G < 2, a, p, (uint32_t)ncur, (uint32_t)begin + first, st);
+      attn_mfma_kernel<kJoint, 4><<<n, 256, 0, st>>>(a, p, (uint32_t)ncur, (uint32_t)begin + first,
+                                                     MOBA_ATTN_TABLES(a));
     });
   };
   if (!in_place) return run(0, ncur + nhist);
