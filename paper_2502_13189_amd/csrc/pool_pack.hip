@@ -4,14 +4,15 @@
 // needs both makes one launch: pool work-groups first, then pack work-groups.
 //
 // Pool (Eq. 6; Algorithm 1 mean_pool): one work-group per (global block,
-// kv-head).  1024 threads = 64 token rows x 16 lanes; each lane owns 8
-// consecutive dims and walks the block's tokens with stride 64, four loads in
-// flight, reading a 256-byte key row per 16 lanes (coalesced).  Sums are kept in fp64
-// and reduced across the rows in a fixed order, so the result is the block mean
-// rounded once to fp32 and is bit-reproducible.  With 16 rows and one load in
-// flight per work-group, a launch of few blocks was bound by latency: 32K tokens, 8
-// heads, B = 2048 (128 work-groups): 72 -> 27 us, K^T pack included (12 us before);
-// 8192 tokens, 32 heads, B = 512: 24 us and 28 for the pack -> 40 us for both.
+// kv-head), 16 lanes to a token row: each lane owns 8 consecutive dims and walks the
+// block's tokens, reading a 256-byte key row per 16 lanes (coalesced).  Sums are kept
+// in fp64 and reduced across the rows in a fixed order, so the result is the block
+// mean rounded once to fp32 and is bit-reproducible.  Two sizes (pool_threads):
+//   256 threads, 16 rows, one load in flight: short blocks, which have no more rows to
+//     read, and batches of many blocks, where the other work-groups of a CU hide the
+//     latency;
+//   1024 threads, 64 rows, four loads in flight: few long blocks, bound by the latency
+//     of one block's loads.
 //
 // V^T pack: four waves per (64-key tile of a sequence, kv-head), each 32 dims and
 // without a barrier.  A wave's 64 x 32 values are staged in LDS and written back as
@@ -21,6 +22,8 @@
 // attn_mfma.hip), so each lane reads its 8 keys as one 16-byte LDS load.
 // Keys past the end of the sequence are stored as zeros.
 #include "moba_internal.h"
+
+#include <algorithm>
 
 namespace moba {
 namespace {
@@ -51,15 +54,14 @@ struct Load8<float> {
   }
 };
 
-constexpr int kThreads = 1024;
-constexpr int kPoolRows = kThreads / 16;  // token rows a pool work-group reads at a time
-constexpr int kPoolAhead = 4;             // loads in flight per thread
 constexpr int kPackRow = 32 + 2;
+
+constexpr int kPoolSums = 16;  // partial sums of a block: 16 rows, or 16 waves
 
 // kterm (nullable): the block keys split exactly into three bf16 planes,
 // kbar = hi + mid + lo, each plane [nblk_total, Hkv, D] (read by the
-// matrix-core gate).
-template <typename T>
+// matrix-core gate).  THREADS / 16 token rows at a time.
+template <typename T, int THREADS>
 __device__ __forceinline__ void pool_block(const T* __restrict__ k, int64_t k_st, int64_t k_sh,
                                            const SeqInfo* __restrict__ seqs, const Problem& p, int b,
                                            int g, float* __restrict__ kbar,
@@ -70,6 +72,8 @@ __device__ __forceinline__ void pool_block(const T* __restrict__ k, int64_t k_st
   const int j = b - sq.blk_off;
   const int64_t t0 = (int64_t)sq.tok_start + (int64_t)j * p.B;
   const int n = (int)min((int64_t)p.B, (int64_t)sq.len - (int64_t)j * p.B);
+  constexpr int kPoolRows = THREADS / 16;
+  constexpr int kPoolAhead = THREADS > 256 ? 4 : 1;  // loads in flight per thread
   const int row = threadIdx.x >> 4;
   const int d0 = (threadIdx.x & 15) * 8;
   const T* src = k + t0 * k_st + (int64_t)g * k_sh + d0;
@@ -93,22 +97,27 @@ __device__ __forceinline__ void pool_block(const T* __restrict__ k, int64_t k_st
 #pragma unroll
     for (int i = 0; i < 8; i++) acc[i] += (double)f[i];
   }
-  // the wave's four rows, then the 16 waves
+  if constexpr (THREADS == 256) {
 #pragma unroll
-  for (int i = 0; i < 8; i++) {
-    acc[i] += __shfl_xor(acc[i], 16, 64);
-    acc[i] += __shfl_xor(acc[i], 32, 64);
-  }
-  const int wave = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) < 16) {
+    for (int i = 0; i < 8; i++) red[row][d0 + i] = acc[i];
+  } else {
+    // the wave's four rows, then the waves
 #pragma unroll
-    for (int i = 0; i < 8; i++) red[wave][d0 + i] = acc[i];
+    for (int i = 0; i < 8; i++) {
+      acc[i] += __shfl_xor(acc[i], 16, 64);
+      acc[i] += __shfl_xor(acc[i], 32, 64);
+    }
+    const int wave = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) < 16) {
+#pragma unroll
+      for (int i = 0; i < 8; i++) red[wave][d0 + i] = acc[i];
+    }
   }
   __syncthreads();
   if (threadIdx.x < kHeadDim) {
     double sum = 0.0;
 #pragma unroll
-    for (int r = 0; r < kThreads / 64; r++) sum += red[r][threadIdx.x];
+    for (int r = 0; r < kPoolSums; r++) sum += red[r][threadIdx.x];
     const float m = (float)(sum / (double)n);
     const int64_t o = ((int64_t)b * p.Hkv + g) * kHeadDim + threadIdx.x;
     kbar[o] = m;
@@ -188,23 +197,23 @@ __global__ __launch_bounds__(256) void pack_kernel(const __hip_bfloat16* __restr
   pack_tile(v, v_st, v_sh, seqs, p, blockIdx.x, blockIdx.y, wave, vt, tile[wave]);
 }
 
-// Work-groups [0, npool): pool (block, kv-head); then pack (kPackTiles tiles, kv-head).
+// Work-groups [0, npool): pool (block, kv-head); then pack (a tile per four waves, kv-head).
 // first: this launch's first work-group.
-constexpr int kPackTiles = kThreads / 256;  // tiles per pack work-group, four waves each
-template <typename T, bool PACK>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8)))
+template <typename T, bool PACK, int THREADS>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(8)))
 void pool_pack_kernel(
     const T* __restrict__ k, int64_t k_st, int64_t k_sh, const __hip_bfloat16* __restrict__ v,
     int64_t v_st, int64_t v_sh, const SeqInfo* __restrict__ seqs, Problem p, uint32_t first,
     uint32_t npool, float* __restrict__ kbar, __hip_bfloat16* __restrict__ kterm, __hip_bfloat16* __restrict__ vt) {
-  constexpr size_t kPoolLds = sizeof(double) * (kThreads / 64) * kHeadDim;
-  constexpr size_t kPackLds = sizeof(uint16_t) * (kThreads / 64) * kKeyTile * kPackRow;
+  constexpr int kPackTiles = THREADS / 256;
+  constexpr size_t kPoolLds = sizeof(double) * kPoolSums * kHeadDim;
+  constexpr size_t kPackLds = sizeof(uint16_t) * (THREADS / 64) * kKeyTile * kPackRow;
   __shared__ __attribute__((aligned(16))) char lds[PACK && kPackLds > kPoolLds ? kPackLds : kPoolLds];
   const uint32_t x = first + blockIdx.x;
   if (x < npool) {
-    pool_block<T>(k, k_st, k_sh, seqs, p, (int)(x % (uint32_t)p.nblk_total),
-                  (int)(x / (uint32_t)p.nblk_total), kbar, kterm,
-                  reinterpret_cast<double(*)[kHeadDim]>(lds));
+    pool_block<T, THREADS>(k, k_st, k_sh, seqs, p, (int)(x % (uint32_t)p.nblk_total),
+                           (int)(x / (uint32_t)p.nblk_total), kbar, kterm,
+                           reinterpret_cast<double(*)[kHeadDim]>(lds));
     return;
   }
   if constexpr (PACK) {
@@ -218,22 +227,51 @@ void pool_pack_kernel(
   }
 }
 
+template <typename T, bool PACK, int THREADS>
+hipError_t launch_threads(const T* k, int64_t k_st, int64_t k_sh, const __hip_bfloat16* v,
+                          int64_t v_st, int64_t v_sh, const SeqInfo* seqs, const Problem& p,
+                          float* kbar, __hip_bfloat16* kterm, __hip_bfloat16* vt, hipStream_t st) {
+  constexpr int kPackTiles = THREADS / 256;
+  const int64_t npool = (int64_t)p.nblk_total * p.Hkv;
+  const int64_t npack = PACK ? (p.vt_tiles + kPackTiles - 1) / kPackTiles * p.Hkv : 0;
+  return launch_pieces(npool + npack, THREADS, [&](uint32_t first, unsigned n) {
+    pool_pack_kernel<T, PACK, THREADS><<<n, THREADS, 0, st>>>(
+        k, k_st, k_sh, v, v_st, v_sh, seqs, p, first, (uint32_t)npool, kbar, kterm, vt);
+  });
+}
+
+// Threads per pool work-group: 256 where a block has no more than 128 rows, or where
+// there are so many (kv-head, block) pairs that 1024 threads have nothing left to hide
+// (2048: eight work-groups of 256 on every CU).  Block means alone, with 1024 -> 256
+// threads: B = 64: 32768 pairs 239 -> 132 us, 2048 pairs 18.8 -> 8.5, 128 pairs 6.6 ->
+// 6.2; B = 256: 512 pairs 9.0 -> 8.8, 128 pairs 6.7 -> 7.6; B = 512: 4096 pairs 120 -> 96,
+// 1024 pairs 23.6 -> 22.8, 256 pairs 7.7 -> 11.8; B = 1024: 2048 pairs 123 -> 98, 512 pairs
+// 24 -> 30; B = 4096: 512 pairs 105 -> 155.  With the pack beside them the line is the
+// same (65536 tokens, 32 kv-heads, B = 64: 455 -> 371 us; B = 512: 361 -> 338).
+int pool_threads(const Problem& p) {
+  const int64_t pairs = (int64_t)p.nblk_total * p.Hkv;
+  return p.B <= 128 || pairs >= std::min<int64_t>(2 * (int64_t)p.B, 2048) ? 256 : 1024;
+}
+
+template <typename T, bool PACK>
+hipError_t launch_typed(const T* k, int64_t k_st, int64_t k_sh, const __hip_bfloat16* v,
+                        int64_t v_st, int64_t v_sh, const SeqInfo* seqs, const Problem& p,
+                        float* kbar, __hip_bfloat16* kterm, __hip_bfloat16* vt, hipStream_t st) {
+  if (pool_threads(p) == 256)
+    return launch_threads<T, PACK, 256>(k, k_st, k_sh, v, v_st, v_sh, seqs, p, kbar, kterm, vt, st);
+  return launch_threads<T, PACK, 1024>(k, k_st, k_sh, v, v_st, v_sh, seqs, p, kbar, kterm, vt, st);
+}
+
 }  // namespace
 
 hipError_t launch_pool(const void* k, bool bf16, int64_t k_st, int64_t k_sh, const SeqInfo* seqs,
                        const Problem& p, float* kbar, __hip_bfloat16* kterm, hipStream_t st) {
   if (p.nblk_total == 0) return hipSuccess;
-  const int64_t npool = (int64_t)p.nblk_total * p.Hkv;
-  return launch_pieces(npool, kThreads, [&](uint32_t first, unsigned n) {
-    if (bf16)
-      pool_pack_kernel<__hip_bfloat16, false><<<n, kThreads, 0, st>>>(
-          static_cast<const __hip_bfloat16*>(k), k_st, k_sh, nullptr, 0, 0, seqs, p, first,
-          (uint32_t)npool, kbar, kterm, nullptr);
-    else
-      pool_pack_kernel<float, false><<<n, kThreads, 0, st>>>(
-          static_cast<const float*>(k), k_st, k_sh, nullptr, 0, 0, seqs, p, first, (uint32_t)npool,
-          kbar, kterm, nullptr);
-  });
+  if (bf16)
+    return launch_typed<__hip_bfloat16, false>(static_cast<const __hip_bfloat16*>(k), k_st, k_sh,
+                                               nullptr, 0, 0, seqs, p, kbar, kterm, nullptr, st);
+  return launch_typed<float, false>(static_cast<const float*>(k), k_st, k_sh, nullptr, 0, 0, seqs,
+                                    p, kbar, kterm, nullptr, st);
 }
 
 hipError_t launch_pack(const __hip_bfloat16* v, int64_t v_st, int64_t v_sh, const SeqInfo* seqs,
@@ -248,12 +286,8 @@ hipError_t launch_pool_pack(const __hip_bfloat16* k, int64_t k_st, int64_t k_sh,
                             const SeqInfo* seqs, const Problem& p, float* kbar,
                             __hip_bfloat16* kterm, __hip_bfloat16* vt, hipStream_t st) {
   if (p.vt_tiles == 0) return hipSuccess;
-  const int64_t npool = (int64_t)p.nblk_total * p.Hkv;
-  const int64_t npack = (p.vt_tiles + kPackTiles - 1) / kPackTiles * p.Hkv;
-  return launch_pieces(npool + npack, kThreads, [&](uint32_t first, unsigned n) {
-    pool_pack_kernel<__hip_bfloat16, true><<<n, kThreads, 0, st>>>(
-        k, k_st, k_sh, v, v_st, v_sh, seqs, p, first, (uint32_t)npool, kbar, kterm, vt);
-  });
+  return launch_typed<__hip_bfloat16, true>(k, k_st, k_sh, v, v_st, v_sh, seqs, p, kbar, kterm, vt,
+                                            st);
 }
 
 }  // namespace moba

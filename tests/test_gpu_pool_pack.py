@@ -30,6 +30,18 @@ def test_block_means(B, dtype):
     assert np.all(np.abs(kbar - ref) <= 2.0 ** -23 * np.abs(ref) + 1e-12 * kabs)
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("B,n", [(128, 3), (129, 3), (129, 32), (129, 33), (1100, 255), (1100, 256)])
+def test_block_means_of_both_sizes(B, n, dtype):
+    """Either side of the line between the two work-group sizes (B = 128; pairs of 8
+    kv-heads and n blocks at twice B and at 2048), a short last block."""
+    T = n * B - 5
+    _, k, _, cu = inputs.make((T,), 8, 8, 128, dtype, B, 0.5, B + n, device=DEV)
+    kbar = binding.pool(k, cu, B).cpu().numpy().astype(np.float64)
+    ref, kabs = oracle.pool(inputs.to_oracle(k), cu.numpy(), B, with_abs=True)
+    assert np.all(np.abs(kbar - ref) <= 2.0 ** -23 * np.abs(ref) + 1e-12 * kabs)
+
+
 @pytest.mark.parametrize("seqlens", [(1,), (63, 65), (64, 0, 128, 1), (257, 191)])
 def test_packed_tiles(seqlens):
     """1 to 4 tiles in the last work-group of four; V beyond a sequence's end is the
