@@ -159,10 +159,16 @@ __device__ __forceinline__ void store_staged(__hip_bfloat16* base, const u32x4* 
   }
 }
 
+// Joint grid: work-groups per tile of a single block (its tiles hold no more rows than
+// the block; a second one of 128 rows would find none).
+__host__ __device__ inline uint32_t block_parts(const Problem& p) {
+  return (int64_t)p.B * p.G <= kRows / 2 ? 1 : 2;
+}
+
 // NW waves: 32 NW query rows per work-group, kRows / (32 NW) work-groups per
 // plan tile.  ncur: work-groups of causal tiles, first in a joint grid (a
-// multiple of 8; the longest tiles start early); first: the first work-group of
-// this piece of a joint grid.
+// multiple of 8; the longest tiles start early); first: the launch's first work-group
+// (joint and current-block grids).
 // (Waves do not pass over key tiles past their last row: the work-group's other waves
 // need them and the barrier holds all.  A branch for it cost 1-3% of the dense kernel at 1K-16K
 // tokens and 1-4 heads per kv-head, 0-2% of the others, and gained nowhere.)
@@ -183,7 +189,7 @@ void attn_mfma_kernel(AttnArgs a, Problem p, uint32_t ncur, uint32_t first,
   const int qc = lane & 31, hh = lane >> 5;
 
   // ------------------------------------------------------------ tile setup
-  const uint32_t bx = MODE == kJoint ? first + blockIdx.x : blockIdx.x;
+  const uint32_t bx = MODE == kJoint || MODE == kCur ? first + blockIdx.x : blockIdx.x;
   const bool hist = MODE == kHist || (MODE == kJoint && bx >= ncur);
   int g, s;
   int64_t kbeg, kend, tmin;
@@ -222,16 +228,16 @@ void attn_mfma_kernel(AttnArgs a, Problem p, uint32_t ncur, uint32_t first,
     ri.h = g * p.G + (ok ? (int)((uint32_t)rem % (uint32_t)p.G) : 0);
     ri.dst = (int64_t)(ev - (uint64_t)a.g0 * TG * kh);
   } else {
-    int y = (int)bx, r0 = 0;
-    g = a.g0 + blockIdx.y;
-    if constexpr (MODE == kJoint) {
-      // groups of 8 consecutive tiles of the list sit on the 8 XCDs; the
-      // work-groups of a tile follow each other on its XCD
-      const uint32_t per = (uint32_t)a.ntiles * kSubTiles;
-      g = a.g0 + (int)(bx / per);
-      const uint32_t z = bx % per;
-      y = (int)(z / (8 * kSubTiles) * 8 + z % 8);
-      r0 = (int)(z / 8 % kSubTiles) * kRowsWg;
+    int y, r0 = 0;
+    if constexpr (MODE == kDense) {
+      y = (int)bx;
+      g = a.g0 + blockIdx.y;
+    } else {
+      const TileAt at = causal_at(bx, a.nhead, a.ntiles, (uint32_t)(a.g1 - a.g0), kSubTiles,
+                                  MODE == kJoint ? block_parts(p) : 1);
+      y = at.tile;
+      g = a.g0 + at.g;
+      r0 = at.sub * kRowsWg;
     }
     const CausalTile ct = tiles[y];
     const int nrow = min(kRowsWg, (ct.t1 - ct.t0) * p.G - r0);
@@ -356,10 +362,14 @@ hipError_t launch_attn_hist_bf16(const AttnArgs& a, const Problem& p, int64_t ti
 
 hipError_t launch_attn_causal_bf16(bool dense, const AttnArgs& a, const Problem& p, hipStream_t st) {
   if (a.ntiles <= 0 || a.g1 <= a.g0) return hipSuccess;
-  dim3 grid((unsigned)a.ntiles, a.g1 - a.g0);
-  if (dense) attn_mfma_kernel<kDense, 8><<<grid, 512, 0, st>>>(a, p, 0, 0, MOBA_ATTN_TABLES(a));
-  else attn_mfma_kernel<kCur, 8><<<grid, 512, 0, st>>>(a, p, 0, 0, MOBA_ATTN_TABLES(a));
-  return hipGetLastError();
+  if (dense) {
+    const dim3 grid((unsigned)a.ntiles, a.g1 - a.g0);
+    attn_mfma_kernel<kDense, 8><<<grid, 512, 0, st>>>(a, p, 0, 0, MOBA_ATTN_TABLES(a));
+    return hipGetLastError();
+  }
+  return launch_pieces(a.ntiles * (a.g1 - a.g0), 512, [&](uint32_t first, unsigned n) {
+    attn_mfma_kernel<kCur, 8><<<n, 512, 0, st>>>(a, p, 0, first, MOBA_ATTN_TABLES(a));
+  });
 }
 
 bool attn_bf16_joint(const Problem& p) { return p.B <= kJointMaxBlock; }
@@ -367,7 +377,7 @@ bool attn_bf16_joint(const Problem& p) { return p.B <= kJointMaxBlock; }
 hipError_t launch_attn_joint_bf16(const AttnArgs& a, const Problem& p, int64_t hist_tiles,
                                   bool in_place, hipStream_t st) {
   if (a.ntiles <= 0 || a.g1 <= a.g0) return hipSuccess;
-  const int64_t ncur = a.ntiles * 2 * (a.g1 - a.g0);
+  const int64_t ncur = (a.nhead * 2 + (a.ntiles - a.nhead) * block_parts(p)) * (a.g1 - a.g0);
   const int64_t nhist = (hist_tiles * 2 + 7) / 8 * 8;
   const auto run = [&](int64_t begin, int64_t groups) {
     return launch_pieces(groups, 256, [&](uint32_t first, unsigned n) {

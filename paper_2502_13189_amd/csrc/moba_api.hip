@@ -227,6 +227,7 @@ struct Plan {
   Problem p{};
   std::vector<SeqInfo> seqs;
   std::vector<CausalTile> tiles;
+  int64_t nhead = 0;            // tiles of the head blocks, first in the list
   std::vector<KeyTile> ktiles;  // key tiles of the dK/dV kernel (kTilesCur plans)
   int64_t hist_per_head = 0;  // routed history selections of one query head, summed over tokens
 };
@@ -329,26 +330,26 @@ void build_plan(const std::vector<int32_t>& cu, int Hq, int Hkv, int B, int topk
     // to the 8 XCDs (each with its own L2), so each block's tiles are put on
     // one XCD, with blocks (and single head tiles, which are too much for one
     // XCD together) spread greedily over the XCDs by key work; each XCD then
-    // takes the groups with the longest tiles first, a group's longest tile
-    // first.  Tile x of the list runs on XCD x % 8 (the list is padded with
-    // empty tiles to a multiple of 8).
-    struct Group { int64_t work, longest; std::vector<CausalTile> tiles; };
+    // takes its head tiles, then its blocks, the groups with the longest tiles
+    // first, a group's longest tile first.  Tile x of the list runs on XCD x % 8
+    // (either part is padded with empty tiles to a multiple of 8).
+    struct Group { int64_t work, longest; bool head; std::vector<CausalTile> tiles; };
     std::vector<Group> groups;
     for (int s = 0; s < S; s++) {
       const int64_t L = (int64_t)cu[s + 1] - cu[s];
       const int head = pl->seqs[s].head;
       for (int64_t b0 = 0, b1; b0 < L; b0 = b1) {
         b1 = std::min(L, b0 + (b0 == 0 ? (int64_t)head * B : B));
-        Group gr{0, 0, {}};
+        Group gr{0, 0, b0 == 0 && head > 1, {}};
         for (int64_t t0 = b0; t0 < b1; t0 += tt) {
           const int64_t t1 = std::min(b1, t0 + tt);
           gr.tiles.push_back(CausalTile{s, (int32_t)(cu[s] + t0), (int32_t)(cu[s] + t1),
                                         (int32_t)(cu[s] + b0)});
           gr.work += t1 - b0;
           gr.longest = t1 - b0;
-          if (b0 == 0 && head > 1) {
+          if (gr.head) {
             groups.push_back(std::move(gr));
-            gr = Group{0, 0, {}};
+            gr = Group{0, 0, true, {}};
           }
         }
         if (gr.tiles.empty()) continue;
@@ -366,18 +367,21 @@ void build_plan(const std::vector<int32_t>& cu, int Hq, int Hkv, int B, int topk
       lists[x].push_back(&gr);
       load[x] += gr.work;
     }
-    std::vector<std::vector<CausalTile>> order(kXcd);
-    size_t n = 0;
-    for (int x = 0; x < kXcd; x++) {
-      std::stable_sort(lists[x].begin(), lists[x].end(),
-                       [](const Group* a, const Group* b) { return a->longest > b->longest; });
-      for (const Group* gr : lists[x])
-        order[x].insert(order[x].end(), gr->tiles.begin(), gr->tiles.end());
-      n = std::max(n, order[x].size());
+    for (const bool part : {true, false}) {
+      std::vector<std::vector<CausalTile>> order(kXcd);
+      size_t n = 0;
+      for (int x = 0; x < kXcd; x++) {
+        std::stable_sort(lists[x].begin(), lists[x].end(),
+                         [](const Group* a, const Group* b) { return a->longest > b->longest; });
+        for (const Group* gr : lists[x])
+          if (gr->head == part) order[x].insert(order[x].end(), gr->tiles.begin(), gr->tiles.end());
+        n = std::max(n, order[x].size());
+      }
+      for (size_t k = 0; k < n; k++)
+        for (int x = 0; x < kXcd; x++)
+          pl->tiles.push_back(k < order[x].size() ? order[x][k] : CausalTile{0, 0, 0, 0});
+      if (part) pl->nhead = (int64_t)pl->tiles.size();
     }
-    for (size_t k = 0; k < n; k++)
-      for (int x = 0; x < kXcd; x++)
-        pl->tiles.push_back(k < order[x].size() ? order[x][k] : CausalTile{0, 0, 0, 0});
     // dK/dV key tiles: local block 0 of every sequence first (early blocks
     // collect the longest routed row lists), then block 1, ...
     for (int j = 0; j < nbmax; j++)
@@ -819,6 +823,7 @@ moba_status moba_forward(const moba_tensor* q, const moba_tensor* k, const moba_
   a.entries = rb.entries;
   a.tiles = d_tiles;
   a.ntiles = (int64_t)pl->tiles.size();
+  a.nhead = pl->nhead;
   const bool in_place = share_memory(in.q, vo, p.T, in.bf16 ? 2 : 4);
 
   { Phase ph("pool", stream);  // bf16: and the V^T pack

@@ -52,7 +52,7 @@ struct Problem {
   int64_t hist_words;     // routing-histogram words per kv-head
   int64_t hist_entries;   // routed history selections over all rows and heads
   int64_t all_entries;    // with those of unrouted rows (what the workspace is sized for)
-  int tile_rows;          // query rows per attention work-group (history and causal tiles)
+  int tile_rows;          // query rows per causal tile and per history tile
   bool gate_counts;       // small batch: the gate counts its selections per block, and the
                           // scatter scans the counts itself (route.hip)
   // the selection's layout: row (t, kv-head g, head hl of the group) of sel
@@ -143,6 +143,7 @@ struct AttnArgs {
   // causal tiles
   const CausalTile* tiles;
   int64_t ntiles;
+  int64_t nhead;  // the first nhead tiles (a multiple of 8) are the head blocks'
   // final output (current-block and dense tiles)
   void* out; int64_t o_st, o_sh;
   float* lse;
@@ -171,6 +172,37 @@ hipError_t launch_merge(bool bf16, const AttnArgs& a, const Problem& p, hipStrea
 // Routed history slots of a row of sequence sq at current block c.
 __device__ __forceinline__ int routed_slots(const SeqInfo& sq, const Problem& p, int c) {
   return c < sq.head ? 0 : min(p.topk - 1, c);
+}
+
+// Work-group x of a forward launch over the causal tiles of nkv kv-heads: the kv-head
+// (from the launch's first), the tile of the list and which part of it.  sh and sb
+// work-groups (1 or 2) per head-block and single-block tile.  8 consecutive tiles of the
+// list sit on the 8 XCDs, the work-groups of a tile follow each other on its XCD.  The
+// head blocks' tiles come first, each rank of the list for all kv-heads before the next:
+// they are up to topk blocks long, and one of the last kv-head that starts when the others
+// are done holds up the launch (current-block launch of 16384 tokens, 32/32 heads, B = 2049,
+// top-3: 582 us, one kv-head after the other 770; 24000 tokens, 16/16, B = 3000, top-5: 978 and
+// 1109).  A single block's tiles stay together, sharing K and V in their XCD's L2.
+struct TileAt {
+  int g, tile, sub;
+};
+
+__device__ __forceinline__ TileAt causal_at(uint32_t x, int64_t nhead, int64_t ntiles, uint32_t nkv,
+                                            uint32_t sh, uint32_t sb) {
+  const uint32_t nx = (uint32_t)nhead * sh * nkv;
+  TileAt r;
+  if (x < nx) {
+    const uint32_t z = x / (8 * sh), y = x % (8 * sh);
+    r.g = (int)(z % nkv);
+    r.tile = (int)(z / nkv * 8 + y % 8);
+    r.sub = (int)(y / 8);
+  } else {
+    const uint32_t per = (uint32_t)(ntiles - nhead) * sb, z = (x - nx) % per;
+    r.g = (int)((x - nx) / per);
+    r.tile = (int)(nhead + (sb == 1 ? z : z / 16 * 8 + z % 8));
+    r.sub = (int)(sb == 1 ? 0 : z / 8 % 2);
+  }
+  return r;
 }
 
 // Largest s with key[s] <= x among sequences, skipping empty ones that share

@@ -18,6 +18,10 @@ CASES = [
     ((1100, 1), 64, 64, 512, 2),   # MHA: the head is all but the last, short block
     ((1300,), 128, 2, 16, 31),     # 31 head blocks, 4 tokens per tile; short blocks after them
 ]
+FORWARD_CASES = CASES + [
+    ((2500, 30), 128, 128, 16, 4),  # blocks that fill part of one 128-row work-group
+    ((5200,), 16, 4, 2100, 2),     # a launch of its own for the causal tiles
+]
 
 
 @pytest.fixture(scope="module", autouse=True)
@@ -32,7 +36,7 @@ def routed(q, k, v, cu, B, topk, dtype):
     print("max_abs %.2e lse %.2e ties %d" % (r["max_abs"], r["lse_max_abs"], r["tie_rows"]))
 
 
-@pytest.mark.parametrize("seqlens,hq,hkv,B,topk", CASES)
+@pytest.mark.parametrize("seqlens,hq,hkv,B,topk", FORWARD_CASES)
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 def test_forward(seqlens, hq, hkv, B, topk, dtype):
     q, k, v, cu = inputs.make(seqlens, hq, hkv, 128, dtype, B, 0.5, B, device=DEV)

@@ -25,6 +25,8 @@ def _need_gpu():
     ((900,), 2, 1, 256, 1),             # top-1: causal tiles only
     ((4300,), 1, 1, 2048, 2),           # the longest blocks of the joint launch
     ((4200,), 1, 1, 2049, 2),           # and the first beyond it
+    ((500,), 16, 2, 16, 3),             # 128 rows per block: one work-group each
+    ((500,), 16, 2, 17, 3),             # 136 rows: two
 ])
 def test_joint_tiles(seqlens, hq, hkv, B, topk):
     q, k, v, cu = inputs.make(seqlens, hq, hkv, 128, torch.bfloat16, B, 0.5, B, device=DEV)
