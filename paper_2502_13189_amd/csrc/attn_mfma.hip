@@ -165,8 +165,8 @@ __host__ __device__ inline uint32_t block_parts(const Problem& p) {
   return (int64_t)p.B * p.G <= kRows / 2 ? 1 : 2;
 }
 
-// NW waves: 32 NW query rows per work-group, kRows / (32 NW) work-groups per
-// plan tile.  ncur: work-groups of causal tiles, first in a joint grid (a
+// NW waves: 32 NW query rows per work-group and history tile, kRows / (32 NW)
+// work-groups per causal tile.  ncur: work-groups of causal tiles, first in a joint grid (a
 // multiple of 8; the longest tiles start early); first: the launch's first work-group
 // (joint and current-block grids).
 // (Waves do not pass over key tiles past their last row: the work-group's other waves
@@ -201,18 +201,16 @@ void attn_mfma_kernel(AttnArgs a, Problem p, uint32_t ncur, uint32_t first,
     const int64_t tend = bin_tile_start[a.g1 * nb];
     // XCD-aware order: work-groups go round-robin to the 8 XCDs, so give each
     // XCD a contiguous run of tiles (tiles of one bin share its K/V block).
-    const uint32_t per = MODE == kHist ? gridDim.x / 8 : ((uint32_t)(tend - tbeg) * kSubTiles + 7) / 8;
+    const uint32_t per = MODE == kHist ? gridDim.x / 8 : ((uint32_t)(tend - tbeg) + 7) / 8;
     const uint32_t x = MODE == kHist ? bx : bx - ncur;
     const uint32_t w = (x % 8) * per + x / 8;
-    const int64_t tile = tbeg + w / kSubTiles;
+    const int64_t tile = tbeg + w;
     if (x / 8 >= per || tile >= tend) return;
     const int bin = tile_bin[tile];
     g = bin / p.nblk_total;
     const int b = bin % p.nblk_total;
-    const int64_t e0 = bin_start[bin] + (tile - bin_tile_start[bin]) * kRows +
-                       (w % kSubTiles) * kRowsWg;
+    const int64_t e0 = bin_start[bin] + (tile - bin_tile_start[bin]) * kRowsWg;
     const int n = (int)min((int64_t)kRowsWg, bin_start[bin] + bin_count[bin] - e0);
-    if (kSubTiles > 1 && n <= 0) return;
     s = find_seq(seqs, p.S, b, [](const SeqInfo& x) { return x.blk_off; });
     const SeqInfo sq = seqs[s];
     kbeg = (int64_t)sq.tok_start + (int64_t)(b - sq.blk_off) * p.B;
@@ -378,7 +376,7 @@ hipError_t launch_attn_joint_bf16(const AttnArgs& a, const Problem& p, int64_t h
                                   bool in_place, hipStream_t st) {
   if (a.ntiles <= 0 || a.g1 <= a.g0) return hipSuccess;
   const int64_t ncur = (a.nhead * 2 + (a.ntiles - a.nhead) * block_parts(p)) * (a.g1 - a.g0);
-  const int64_t nhist = (hist_tiles * 2 + 7) / 8 * 8;
+  const int64_t nhist = (hist_tiles + 7) / 8 * 8;
   const auto run = [&](int64_t begin, int64_t groups) {
     return launch_pieces(groups, 256, [&](uint32_t first, unsigned n) {
       attn_mfma_kernel<kJoint, 4><<<n, 256, 0, st>>>(a, p, (uint32_t)ncur, (uint32_t)begin + first,

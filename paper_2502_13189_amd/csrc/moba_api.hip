@@ -793,13 +793,20 @@ moba_status moba_forward(const moba_tensor* q, const moba_tensor* k, const moba_
   const size_t limit = workspace_limit();
   int nch = 0;
   size_t need = 0;
-  for (int n = p.Hkv; n >= 1; n--) {
-    Bump bp(nullptr);
-    FwdBufs b{};
-    forward_layout(p, in.bf16, kk, n, &bp, &b);
-    if (bp.off + kAlign <= limit) { nch = n; need = bp.off + kAlign; break; }
+  // one launch for history and current block takes half as long history tiles, i.e. a
+  // longer list of them: not where the cap has room for the shorter one only
+  bool joint = in.bf16 && attn_bf16_joint(p);
+  for (;; joint = false) {
+    p.tile_rows = joint ? kTileRowsJoint : pl->p.tile_rows;
+    for (int n = p.Hkv; n >= 1; n--) {
+      Bump bp(nullptr);
+      FwdBufs b{};
+      forward_layout(p, in.bf16, kk, n, &bp, &b);
+      if (bp.off + kAlign <= limit) { nch = n; need = bp.off + kAlign; break; }
+    }
+    if (nch > 0) break;
+    if (!joint) return MOBA_ERR_NO_MEMORY;
   }
-  if (nch == 0) return MOBA_ERR_NO_MEMORY;
   // as many chunks as the cap requires, of equal size (the last may be smaller)
   nch = (int)ceil_div(p.Hkv, ceil_div(p.Hkv, nch));
   if ((st = ensure_workspace(dc, need)) != MOBA_OK) return st;
@@ -847,7 +854,7 @@ moba_status moba_forward(const moba_tensor* q, const moba_tensor* k, const moba_
         kh > 0 && e_chunk > 0
             ? ceil_div(e_chunk, p.tile_rows) + (int64_t)(a.g1 - a.g0) * p.nblk_total
             : 0;
-    if (!in.bf16 || attn_bf16_joint(p)) {
+    if (!in.bf16 || joint) {
       Phase ph("attn_hist", stream);  // and the current-block tiles
       MOBA_LAUNCH(in.bf16 ? launch_attn_joint_bf16(a, p, hist_tiles, in_place, stream)
                           : launch_attn_f32(a, p, hist_tiles, in_place, stream));
@@ -1519,7 +1526,7 @@ size_t moba_workspace_bytes(int64_t T, int32_t Hq, int32_t Hkv, int32_t D, int64
   p.G = Hq / Hkv;
   p.nblk_total = (int)std::min<int64_t>(nblk_total, INT32_MAX);
   p.vt_tiles = ceil_div(T, kKeyTile) + nblk_total;
-  p.tile_rows = std::min(kTileRowsMfma, kTileRowsF32);  // the smaller gives more tiles
+  p.tile_rows = std::min(kTileRowsJoint, kTileRowsF32);  // the smaller gives more tiles
   const int kk = (int)std::min<int64_t>(topk, nblk_total);
   p.hist_words = (ceil_div(T, std::max(1, kRouteRows / p.G)) + 1) * nblk_total;
   p.all_entries = T * Hq * (int64_t)(kk - 1);

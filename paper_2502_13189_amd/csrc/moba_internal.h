@@ -10,6 +10,7 @@ namespace moba {
 constexpr int kHeadDim = 128;     // D; every kernel is specialised for it
 constexpr int kKeyTile = 64;      // keys per LDS tile in the attention kernels
 constexpr int kTileRowsMfma = 256;  // query rows per bf16 (matrix-core) attention work-group
+constexpr int kTileRowsJoint = 128;  // history tiles of the joint launch
 constexpr int kTileRowsF32 = 128;   // query rows per fp32 attention work-group
 constexpr int kMaxGroup = 128;      // largest Hq / Hkv
 constexpr int kMaxBlocksPerSeq = 4096;  // limit of the routing kernels' LDS tables
@@ -52,7 +53,8 @@ struct Problem {
   int64_t hist_words;     // routing-histogram words per kv-head
   int64_t hist_entries;   // routed history selections over all rows and heads
   int64_t all_entries;    // with those of unrouted rows (what the workspace is sized for)
-  int tile_rows;          // query rows per causal tile and per history tile
+  int tile_rows;          // query rows per causal tile, entries per history tile (joint
+                          // launch: kTileRowsJoint entries)
   bool gate_counts;       // small batch: the gate counts its selections per block, and the
                           // scatter scans the counts itself (route.hip)
   // the selection's layout: row (t, kv-head g, head hl of the group) of sel

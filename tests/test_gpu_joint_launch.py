@@ -4,7 +4,7 @@ waves without a key in a causal tile's last key tiles, no history at all."""
 import pytest
 import torch
 
-from paper_2502_13189_amd import inputs
+from paper_2502_13189_amd import binding, inputs
 import parity
 
 pytestmark = pytest.mark.gpu
@@ -32,3 +32,32 @@ def test_joint_tiles(seqlens, hq, hkv, B, topk):
     q, k, v, cu = inputs.make(seqlens, hq, hkv, 128, torch.bfloat16, B, 0.5, B, device=DEV)
     r = parity.moba_parity(q, k, v, cu, B, topk, dtype="bf16")
     print("max_abs %.2e lse %.2e" % (r["max_abs"], r["lse_max_abs"]))
+
+
+def test_smallest_workspace(monkeypatch):
+    """Down to the smallest cap that is accepted, where the list of 128-row history tiles
+    no longer fits and the two launches of 256-row ones run: the same bits."""
+    q, k, v, cu = inputs.make((3000, 1500), 4, 2, 128, torch.bfloat16, 32, 0.5, 3, device=DEV)
+    ref, rlse = binding.forward(q, k, v, cu, 32, 12)
+    torch.cuda.synchronize()
+    binding.release_workspace()
+
+    def run(limit):
+        monkeypatch.setenv("MOBA_WORKSPACE_LIMIT_BYTES", str(limit))
+        try:
+            return binding.forward(q, k, v, cu, 32, 12)
+        except binding.MobaError as e:
+            assert e.name == "MOBA_ERR_NO_MEMORY"
+            return None
+
+    lo, hi = 0, binding.workspace_bytes(4500, 4, 2, binding.num_blocks(cu, 32), 12)
+    assert run(hi) is not None
+    while hi - lo > 256:
+        mid = (lo + hi) // 2
+        if run(mid) is None:
+            lo = mid
+        else:
+            hi = mid
+    for limit in (hi, hi + 2048, hi + 8192, hi + 65536):
+        out, lse = run(limit)
+        assert torch.equal(out, ref) and torch.equal(lse, rlse)
