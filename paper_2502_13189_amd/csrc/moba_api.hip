@@ -14,6 +14,7 @@
 #include "bwd_internal.h"
 #include "decode_internal.h"
 #include "moba_internal.h"
+#include "plan_rules.h"
 
 #include <algorithm>
 #include <chrono>
@@ -220,7 +221,7 @@ moba_status read_cu(const moba_tensor* cu, int64_t T, hipStream_t stream,
 }
 
 // ------------------------------------------------------------- planning
-// kTilesBwd: kTilesCur without head blocks (the backward of a small top-k).
+// kTilesBwd: kTilesCur without head blocks (a backward that does not take them).
 enum TileMode { kTilesNone = 0, kTilesCur = 1, kTilesDense = 2, kTilesBwd = 3 };
 
 struct Plan {
@@ -233,22 +234,6 @@ struct Plan {
 };
 
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
-
-// Rows of a sequence's first topk blocks keep every past block, i.e. attend
-// their whole prefix: a causal tile then does what routed tiles, their partials
-// and the merge would, and the gate has nothing to choose.  But such a tile is
-// up to topk blocks long, so only where the sequence's causal tiles alone keep
-// half of the chip's 512 128-row work-groups busy for that long.  (Of the
-// sequence alone, so that its rows do not depend on the batch.)  The whole
-// forward, all rows routed, then with the head: 8192 tokens, 32 heads, B = 512,
-// top-3: 366 -> 352 us; 32K tokens, B = 256, top-32: 8.64 -> 7.97 ms; 112K ragged
-// tokens, B = 1024, top-4: 8.93 -> 8.76 ms.
-int head_blocks(int64_t L, int G, int Hkv, int B, int topk) {
-  if (B < 1 || topk < 2) return 1;
-  const double h = (double)std::min<int64_t>(L, (int64_t)topk * B);
-  const double pairs = 0.5 * h * h + 0.5 * B * (L - h);
-  return pairs * G * Hkv / 128 >= 256.0 * h ? topk : 1;
-}
 
 // B = 0 means "one block per sequence" (dense attention).
 void build_plan(const std::vector<int32_t>& cu, int Hq, int Hkv, int B, int topk, TileMode mode,
@@ -286,7 +271,7 @@ void build_plan(const std::vector<int32_t>& cu, int Hq, int Hkv, int B, int topk
     q.gate_off = (int32_t)gate;
     q.rc_off = (int32_t)rc;
     q.hist_off = hw;
-    q.head = heads ? head_blocks(L, p.G, Hkv, B, topk) : 1;
+    q.head = heads ? head_blocks(L, Hq, B, topk) : 1;
     blk += nb;
     vt += ceil_div(L, kKeyTile);
     gate += ceil_div(L, p.gate_tw);
@@ -878,17 +863,9 @@ moba_status moba_forward(const moba_tensor* q, const moba_tensor* k, const moba_
 
 namespace {
 
-// The backward takes the forward's head blocks from this top-k on.  They spare it
-// (topk - 1) / 2 fp32 dQ partials per head row but make its causal dQ tiles long, one
-// work-group per CU.  Forward + backward without and with them, 32/8 heads: 16K
-// tokens, B = 256, top-16: 7.60 -> 7.22 ms; 32K, B = 512, top-8: 12.25 -> 11.97; 16K, B =
-// 1024, top-4: 4.69 -> 4.67; 32K, B = 2048, top-3: 12.18 -> 12.30; 8K tokens, 32 heads, B =
-// 128, top-3: 1.095 -> 1.103.
-constexpr int kBwdHeadTopk = 4;
-
 // dK/dV work-groups per key tile: one work-group fills a CU, so with fewer key
 // tiles (of all kv-heads) than half of the 256 CUs, each tile's rows are shared out.
-// 1518 ragged tokens, 8/2 heads (26 key tiles): 88 us in one piece, 25 + 6 us in 8
+// 1518 ragged tokens, 8/2 heads, B = 128 (28 key tiles): 88 us in one piece, 25 + 6 us in 8
 // with their sum.
 int kv_split(int64_t ktiles) {
   return ktiles > 0 ? (int)std::min<int64_t>(kMaxKvSplit, std::max<int64_t>(1, 256 / ktiles)) : 1;
@@ -950,7 +927,7 @@ moba_status backward_impl(const moba_tensor* q, const moba_tensor* k, const moba
   const SeqInfo* d_seqs;
   const CausalTile* d_tiles;
   const KeyTile* d_ktiles;
-  const TileMode tiles = kk < kBwdHeadTopk ? kTilesBwd : kTilesCur;
+  const TileMode tiles = bwd_head_blocks(in.Hq, block_size, kk) ? kTilesCur : kTilesBwd;
   if ((st = get_plan(dc, stream, in.cu, in.Hq, in.Hkv, block_size, kk, tiles, kTileRowsMfma, &pl,
                      &d_seqs, &d_tiles, &d_ktiles)) != MOBA_OK)
     return st;
