@@ -35,6 +35,8 @@
 // entries keep their places.
 #include "moba_internal.h"
 
+#include <algorithm>
+
 namespace moba {
 namespace {
 
@@ -579,15 +581,21 @@ hipError_t launch_staged(dim3 grid, size_t lds, const int32_t* sel, const SeqInf
 }  // namespace
 
 // The small-batch scatter takes one bin per thread, up to 31 selections per
-// row, and room in LDS beside the staged entries.  Every work-group reads every count, so their product is bounded:
-// 4M words are 16 MB from L2, about the time of one of the launches saved
-// (8192 tokens, 32 heads: 256 work-groups x 16K words).  The counts lie where
-// the partials of a single kv-head fit, so no call needs more workspace.
+// row, and room in LDS beside the staged entries.  A thread adds up its bin's counts over
+// the sequence's gate groups, eight loads at a time and one after the other, so their
+// number is bounded.  Routing kernels, all five then this one: top-3: 32 groups 23 -> 11
+// us, 128 groups 24 -> 18, 256 groups 24 -> 28, 512 groups 25 -> 47; top-12: 128 groups 48 ->
+// 28, 256 groups 50 -> 38, 512 groups 51 -> 56.  Every work-group reads every count, so
+// their product is bounded too: 4M words are 16 MB from L2, about the time of one of the
+// launches saved.  The counts lie where the partials of a single kv-head fit, so no call
+// needs more workspace.
 bool route_gate_counts(const Problem& p) {
   const int64_t kh = p.topk - 1;
   const int64_t nbins = (int64_t)p.Hkv * p.nblk_total;
   const int64_t words = (int64_t)p.Hkv * p.gate_groups * p.nblk_max;
-  return kh >= 1 && kh <= 31 && nbins <= kRouteRows && p.hist_entries > 0 &&
+  // gate groups of the longest sequence, at most
+  const int64_t chain = std::min(p.gate_groups, (int64_t)p.nblk_max * p.B / p.gate_tw + 1);
+  return chain <= (kh < 8 ? 160 : 320) && kh >= 1 && kh <= 31 && nbins <= kRouteRows && p.hist_entries > 0 &&
          p.route_chunks * p.Hkv * words <= (int64_t(4) << 20) &&
          staged_lds_bytes(p.nblk_max, (int)kh) + (size_t)p.nblk_max * 4 + 256 <= kRouteLdsMax &&
          words * 4 <= p.T * p.G * kh * kHeadDim * 2;

@@ -27,6 +27,8 @@ def _need_gpu():
     ((2000,), 4, 1, 16, 32),               # the largest slot count, 125 blocks
     ((8190,), 2, 2, 16, 6),                # 1022 bins, the last ones below the limit
     ((1025, 1023), 16, 16, 64, 3),         # one row past a routing chunk
+    ((2544,), 16, 1, 16, 3),               # 159 gate groups, the last below the limit
+    ((5104,), 16, 1, 64, 9),               # 319, from eight selections per row on
 ])
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 def test_small_routing_equals_general(seqlens, hq, hkv, B, topk, dtype):
