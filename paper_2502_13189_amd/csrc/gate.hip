@@ -253,7 +253,9 @@ __device__ __forceinline__ void insert_value(float (&lc)[KM], float sj) {
 // wave's loads and products overlap the other's selection work; at 31 places
 // that spills some registers and is still faster (top-31 over 128 blocks:
 // 0.45 vs 0.53 ms with one wave per SIMD and no spills).
-template <int KM>
+// COUNT: also leave the group's counts (gcount); apart, as the counting costs the
+// list of 11 places four more spilled registers (3% of the gate at 64K tokens, top-12).
+template <int KM, bool COUNT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KM <= 31 ? 2 : 1)))
 void gate_mfma_kernel(const __hip_bfloat16* __restrict__ q, int64_t q_st, int64_t q_sh,
                       const __hip_bfloat16* __restrict__ kterm, const SeqInfo* __restrict__ seqs,
@@ -451,7 +453,7 @@ void gate_mfma_kernel(const __hip_bfloat16* __restrict__ q, int64_t q_st, int64_
       __builtin_amdgcn_wave_barrier();
     }
   }
-  if (gcount)
+  if constexpr (COUNT)
     count_kept<KM>(reinterpret_cast<int32_t*>(terms), sq.nblk, valid, li, c, K, sq.head,
                    gcount + ((int64_t)g * p.gate_groups + blockIdx.x) * p.nblk_max);
   if (!valid || (sq.head > 1 && c < sq.head)) return;
@@ -463,10 +465,14 @@ hipError_t launch_km(const void* q, int64_t q_st, int64_t q_sh, const float* kba
                      const __hip_bfloat16* kterm, const SeqInfo* seqs, const Problem& p,
                      int32_t* sel, float* scores, int nmax, int32_t* gcount, hipStream_t st) {
   dim3 grid((unsigned)p.gate_groups, p.Hkv);
-  if constexpr (std::is_same<T, __hip_bfloat16>::value)
-    gate_mfma_kernel<KM><<<grid, 256, 0, st>>>(static_cast<const T*>(q), q_st, q_sh, kterm, seqs,
-                                               p, sel, scores, nmax, gcount);
-  else
+  if constexpr (std::is_same<T, __hip_bfloat16>::value) {
+    if (gcount)
+      gate_mfma_kernel<KM, true><<<grid, 256, 0, st>>>(static_cast<const T*>(q), q_st, q_sh, kterm,
+                                                       seqs, p, sel, scores, nmax, gcount);
+    else
+      gate_mfma_kernel<KM, false><<<grid, 256, 0, st>>>(static_cast<const T*>(q), q_st, q_sh, kterm,
+                                                        seqs, p, sel, scores, nmax, nullptr);
+  } else
     gate_kernel<T, KM><<<grid, 256, 0, st>>>(static_cast<const T*>(q), q_st, q_sh, kbar, seqs, p,
                                              sel, scores, nmax, gcount);
   return hipGetLastError();
