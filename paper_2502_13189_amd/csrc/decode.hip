@@ -42,6 +42,8 @@
 
 #include <math.h>
 
+#include <type_traits>
+
 namespace moba {
 namespace {
 
@@ -98,10 +100,12 @@ __global__ __launch_bounds__(256) void decode_gate_kernel(DecodeArgs a, Problem 
 #pragma unroll
     for (int i = 0; i < 4; i++) qw[i] = reinterpret_cast<const uint4*>(qr)[i];
   }
-  for (int j0 = 0; j0 < c; j0 += kGatePass) {
-    float4 kv[kGateAhead][8];
+  // one pass from block j0: AHEAD x 64 blocks
+  const auto pass = [&](int j0, auto ahead) {
+    constexpr int kAhead = decltype(ahead)::value;
+    float4 kv[kAhead][8];
 #pragma unroll
-    for (int e = 0; e < kGateAhead; e++) {
+    for (int e = 0; e < kAhead; e++) {
       const int j = min(j0 + 64 * e + (tid >> 2), c - 1);  // past the candidates: re-read, unused
       const float4* kr = reinterpret_cast<const float4*>(
           a.kbar + ((int64_t)(sq.blk_off + j) * p.Hkv + g) * kHeadDim + 32 * quarter);
@@ -109,7 +113,7 @@ __global__ __launch_bounds__(256) void decode_gate_kernel(DecodeArgs a, Problem 
       for (int i = 0; i < 8; i++) kv[e][i] = kr[i];
     }
 #pragma unroll
-    for (int e = 0; e < kGateAhead; e++) {
+    for (int e = 0; e < kAhead; e++) {
       float acc = 0.0f;
 #pragma unroll
       for (int i = 0; i < 8; i++) {
@@ -124,6 +128,12 @@ __global__ __launch_bounds__(256) void decode_gate_kernel(DecodeArgs a, Problem 
       // NaN counts as -inf, so that the order is total and exactly nh blocks are kept
       if (quarter == 0 && j < c) sc[j] = fmaxf(((acc + p1) + p2) + p3, -INFINITY);
     }
+  };
+  for (int j0 = 0; j0 < c; j0 += kGatePass) {
+    // (a row of few blocks would otherwise read its last one over and over)
+    if (c - j0 > 128) pass(j0, std::integral_constant<int, kGateAhead>{});
+    else if (c - j0 > 64) pass(j0, std::integral_constant<int, 2>{});
+    else pass(j0, std::integral_constant<int, 1>{});
   }
   if (tid < 4) sc[c + tid] = -INFINITY;  // the rank loop reads whole groups of four
   __syncthreads();

@@ -27,6 +27,7 @@ def _need_gpu():
     ((5000, 2), 16, 1, 300, 3),                   # all 16 head columns; chunks end inside blocks
     ((2100,), 2, 2, 8, 9),                        # 263 blocks: a second gate pass
     ((2060, 300), 1, 1, 2, 12),                   # 1030 blocks: selection by argmax rounds
+    ((513, 521, 1025, 1033, 2571), 2, 1, 8, 5),   # 64, 65, 128, 129, 321 past blocks: passes of 64 to 256
     ((17000,), 8, 1, 64, 64),                     # one combine share of 64 slots
 ])
 @pytest.mark.parametrize("mode", ["moba", "full"])
