@@ -96,7 +96,8 @@ def launch_keys(seqlens, B, topk, hq):
     """(causal, routed) keys per query head: attended_keys() split as the
     kernels take them.  Rows of a sequence's first topk blocks attend their
     whole prefix in the causal tiles where the sequence is large enough
-    (head_blocks in moba_api.hip)."""
+    (head_blocks in csrc/plan_rules.h, which tests/test_plan_rules.py compares
+    with this)."""
     cur, hist, _ = attended_keys(seqlens, B, topk)
     head = 0
     for L in seqlens:
@@ -104,6 +105,11 @@ def launch_keys(seqlens, B, topk, hq):
         if topk >= 2 and h > 0 and (0.5 * h * h + 0.5 * B * (L - h)) * hq / 128 >= 256.0 * h:
             head += attended_keys([h], B, topk)[1]
     return cur + head, hist - head
+
+
+def backward_takes_heads(hq, B, topk):
+    """bwd_head_blocks in csrc/plan_rules.h (compared by the same test)."""
+    return topk >= 4 and hq * (topk - 1) * (1.0 - B / 4600.0) >= 130.0
 
 
 def dense_keys(seqlens):
@@ -344,9 +350,8 @@ def run_backward(args):
     binding.profile_enable(False)
     phases = binding.profile_read()
     cur, hist, _ = attended_keys(w.seqlens, w.block_size, w.topk)
-    # (the backward routes every row below top-4)
-    causal, routed = (launch_keys(w.seqlens, w.block_size, w.topk, w.hq) if w.topk >= 4
-                      else (cur, hist))
+    causal, routed = (launch_keys(w.seqlens, w.block_size, w.topk, w.hq)
+                      if backward_takes_heads(w.hq, w.block_size, w.topk) else (cur, hist))
     pairs = w.hq * (cur + hist)
     flop = 10.0 * w.d * pairs
     tflops = flop / (ms * 1e-3) / 1e12
