@@ -4,7 +4,8 @@
 // causal attention (Eq. 1), from one kernel template.
 //
 // Work-group = 8 waves = 256 query rows, one work-group per CU, or 4 waves = 128
-// rows, two per CU (two waves per SIMD either way; see kJointMaxBlock); wave w
+// rows, two per CU (two waves per SIMD either way; see kJointMaxBlock and
+// hist_persist); wave w
 // owns rows 32w..32w+31, one query per lane column.  Sharing each K/V tile among
 // 256 rows halves the LDS writes and DMA instructions per row.
 // Keys are consumed in tiles of 64.  LDS holds two K buffers and two V^T
@@ -49,6 +50,8 @@
 
 #include <math.h>
 
+#include <algorithm>
+
 namespace moba {
 namespace {
 
@@ -61,10 +64,12 @@ constexpr float kSumLimit = 256.0f;  // largest per-lane weight sum kept without
 // 4-wave work-groups (128 rows, two per CU): one's start (finding its rows,
 // gathering them) and epilogue run beside the other's key loop, and 128-row
 // causal tiles mask less.  Longer blocks run 8-wave work-groups (one per CU), which
-// read each K/V tile half as often.  Both launches' time, 8-wave then 4-wave: B = 512,
+// read each K/V tile half as often; large batches of short blocks a persistent history
+// kernel (see hist_persist).  Both launches' time, 8-wave then 4-wave: B = 512,
 // 8K tokens, 32 heads: 289 -> 260 us; B = 128, 1033 tokens, 8/2 heads: 22 -> 10 us; B =
 // 2048, 32K tokens, 32/8 heads: 2454 -> 2422 us; B = 4096, 1M tokens: 670 -> 698 ms.
 constexpr int kJointMaxBlock = 2048;
+constexpr int kCus = 256;
 constexpr float kLn2 = 0.69314718055994531f;
 
 // Weights of S under the running max m as bf16 P^T operands pb[2*th + s2]
@@ -345,6 +350,182 @@ void attn_mfma_kernel(AttnArgs a, Problem p, uint32_t ncur, uint32_t first,
   store_staged(static_cast<__hip_bfloat16*>(hist ? a.o_part : a.out), stage, sdst, wave, lane);
 }
 
+// ----------------------------------------------------------------------
+// History tiles of short blocks in large batches, persistent: one work-group per CU
+// walks a run of tiles.  With one or two key tiles per history tile, the per-tile cost
+// outside the key loop (work-group start, routed query rows, first K/V tile, epilogue)
+// dominates; here the next tile's query rows and first K/V tile are fetched during the
+// current tile's last key tile.
+struct HistCtx {
+  int g, s;
+  int64_t kbeg, kend, tok0;
+  int i0, i1;
+  RowInfo ri;
+};
+
+__device__ __forceinline__ bool hist_setup(const AttnArgs& a, const Problem& p, int64_t tile,
+                                           int64_t tlim, int rloc, HistCtx& c) {
+  if (tile >= tlim) return false;
+  const int bin = a.tile_bin[tile];
+  const int g = bin / p.nblk_total, b = bin % p.nblk_total;
+  const int64_t e0 = a.bin_start[bin] + (tile - a.bin_tile_start[bin]) * kRows;
+  const int n = (int)min((int64_t)kRows, a.bin_start[bin] + a.bin_count[bin] - e0);
+  const int s = find_seq(a.seqs, p.S, b, [](const SeqInfo& x) { return x.blk_off; });
+  const SeqInfo sq = a.seqs[s];
+  const int64_t kbeg = (int64_t)sq.tok_start + (int64_t)(b - sq.blk_off) * p.B;
+  const uint32_t kh = (uint32_t)(p.topk - 1);
+  const uint64_t TG = (uint64_t)p.T * p.G;  // (below 2^32)
+  const uint32_t ev = a.entries[e0 + min(rloc, n - 1)];
+  const uint64_t rem = ev / kh - (uint64_t)g * TG;
+  const bool ok = rem < TG;
+  c.ri.valid = rloc < n && ok;
+  c.ri.t = ok ? (int64_t)((uint32_t)rem / (uint32_t)p.G) : kbeg;
+  c.ri.h = g * p.G + (ok ? (int)((uint32_t)rem % (uint32_t)p.G) : 0);
+  c.ri.dst = (int64_t)(ev - (uint64_t)a.g0 * TG * kh);
+  c.g = __builtin_amdgcn_readfirstlane(g);
+  c.s = __builtin_amdgcn_readfirstlane(s);
+  c.kbeg = uniform64(kbeg);
+  c.kend = uniform64(kbeg + p.B);
+  c.tok0 = uniform64(sq.tok_start);
+  c.i0 = (int)((c.kbeg - c.tok0) / kKeyTile);
+  c.i1 = (int)((c.kend - c.tok0 + kKeyTile - 1) / kKeyTile);
+  return true;
+}
+
+// The tile-dependent (wave-uniform) part of the DMA sources.
+__device__ __forceinline__ void dma_tile(Dma<8>& D, const AttnArgs& a, const Problem& p,
+                                         const HistCtx& c) {
+  const SeqInfo sq = a.seqs[c.s];
+  const int64_t kst = a.k_st * 2;
+  D.kbase = reinterpret_cast<const char*>(static_cast<const __hip_bfloat16*>(a.k) +
+                                          (int64_t)c.g * a.k_sh) + c.tok0 * kst;
+  D.len = sq.len;
+  D.klast = D.kbase + (sq.len - 1) * kst;
+  D.vbase = reinterpret_cast<const char*>(
+      a.vt + ((int64_t)c.g * p.vt_tiles + sq.vt_tile_off) * (kKeyTile * kHeadDim));
+}
+
+__device__ __forceinline__ void load_q(bf16x8 (&qf)[8], const AttnArgs& a, const RowInfo& ri,
+                                       int hh) {
+  const __hip_bfloat16* qrow = static_cast<const __hip_bfloat16*>(a.q) + ri.t * a.q_st +
+                               (int64_t)ri.h * a.q_sh + 8 * hh;
+#pragma unroll
+  for (int kk = 0; kk < 8; kk++)
+    qf[kk] = as_bf16x8(*reinterpret_cast<const u32x4*>(qrow + 16 * kk));
+}
+
+__global__ __launch_bounds__(512, 1) void attn_hist_persist_kernel(AttnArgs a, Problem p) {
+  __shared__ u32x4 lds[kLdsChunks];
+  __shared__ u32x4 stage[kRows * kStageRow];  // the tile's partial rows (bf16)
+  __shared__ int64_t sdst[kRows];             // their destinations (-1: no row)
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = tid >> 6;
+  const int qc = lane & 31, hh = lane >> 5;
+  const int rloc = wave * 32 + qc;
+
+  // XCD-aware walk: work-groups go round-robin to the 8 XCDs; XCD x owns
+  // the contiguous run [x*per, (x+1)*per) of the tiles (tiles of one bin share
+  // its K/V block), and its work-groups take every nx-th tile of it.  Every
+  // work-group leaves the loop once its next tile is past the run.
+  const int64_t nb = p.nblk_total;
+  const int64_t tbeg = a.bin_tile_start[a.g0 * nb];
+  const int64_t tend = a.bin_tile_start[a.g1 * nb];
+  const int64_t nx = gridDim.x / 8;
+  const int64_t per = (tend - tbeg + 7) / 8;
+  const int64_t xs = tbeg + (int64_t)(blockIdx.x % 8) * per;
+  const int64_t tlim = min(tend, xs + per);
+  int64_t tile = xs + blockIdx.x / 8;
+
+  HistCtx c;
+  if (!hist_setup(a, p, tile, tlim, rloc, c)) return;
+  bf16x8 qf[8];
+  load_q(qf, a, c.ri, hh);
+  Dma<8> D;
+  dma_lanes(D, __builtin_amdgcn_readfirstlane(wave), lane, a.k_st * 2);
+  dma_tile(D, a, p, c);
+  ReadOff ro;
+  ro.kq = qc * kRowK + hh;
+  ro.vq = qc * kRowV + hh;
+  const float c2 = a.scale_log2;
+
+  dma_k(D, c.i0, lds);
+  dma_v(D, c.i0, lds + 2 * kBufK);
+  dma_wait();
+  __syncthreads();
+
+  int par = 0;  // buffer holding the current key tile
+  for (;;) {
+    HistCtx n;
+    const bool more = hist_setup(a, p, tile + nx, tlim, rloc, n);
+    Dma<8> Dn = D;
+    if (more) dma_tile(Dn, a, p, n);
+    f32x16 o[4];
+    float m = -INFINITY, l = 0.0f;
+#pragma unroll
+    for (int dt = 0; dt < 4; dt++)
+#pragma unroll
+      for (int r = 0; r < 16; r++) o[dt][r] = 0.0f;
+    f32x16 sc[2];
+    bf16x8 pb[4];
+    for (int i = c.i0; i < c.i1; i++) {
+      const int cur = par;
+      par ^= 1;
+      const bool last = i + 1 == c.i1;
+      if (!last) {
+        dma_k(D, i + 1, lds + (cur ^ 1) * kBufK);
+        dma_v(D, i + 1, lds + 2 * kBufK + (cur ^ 1) * kBufV);
+      } else if (more) {
+        dma_k(Dn, n.i0, lds + (cur ^ 1) * kBufK);
+        dma_v(Dn, n.i0, lds + 2 * kBufK + (cur ^ 1) * kBufV);
+      }
+      qk(sc, lds + cur * kBufK, ro, qf);
+      if (last && more) load_q(qf, a, n.ri, hh);  // this tile's products are issued
+      const int64_t u0 = c.tok0 + (int64_t)i * kKeyTile;
+      const bool edge = u0 < c.kbeg || u0 + kKeyTile > c.kend;
+      int lo = 0, hi = kKeyTile;
+      if (edge) {
+        lo = (int)max((int64_t)0, c.kbeg - u0) - 4 * hh;
+        hi = (int)min((int64_t)kKeyTile, c.kend - u0) - 4 * hh;
+      }
+      softmax<kHist>(sc, m, l, o, pb, edge, lo, hi, c2);
+      pv(o, lds + 2 * kBufK + cur * kBufV, ro, pb);
+      dma_wait();
+      __syncthreads();
+    }
+    // epilogue: the normalised partial (bf16) and its lse
+    const float l_tot = l + xor32(l);  // every lane takes part in the exchange
+    stage_row(o, 1.0f / l_tot, stage, rloc, hh);
+    if (hh == 0) sdst[rloc] = c.ri.valid ? c.ri.dst * kHeadDim : -1;
+    if (c.ri.valid && hh == 0) a.lse_part[c.ri.dst] = (m + __builtin_amdgcn_logf(l_tot)) * kLn2;
+    __syncthreads();
+    store_staged(static_cast<__hip_bfloat16*>(a.o_part), stage, sdst, wave, lane);
+    // the staging area is rewritten only after the next tile's key loop,
+    // whose barriers order these reads before those writes
+    if (!more) break;
+    c = n;
+    D = Dn;
+    tile += nx;
+  }
+}
+
+}  // namespace
+
+namespace {
+
+// Where the persistent kernel and a launch for the current-block tiles beat the joint
+// launch: full history tiles (their mean number per bin, from the planned entries),
+// many for every CU, over few key tiles.  Both kinds of attention launches, joint /
+// persistent, by entries per bin and 256-row tiles per CU: 128-256 and any number
+// 0.57-0.81; 512-1024 and any 0.90-1.08; from 1024 on, 64 tiles per CU and more: B = 16-64
+// 1.03-1.19 (one 0.95), B = 100-192 0.94-1.06; from 2048 on: B = 16-64 1.05-1.23, B =
+// 100-192 0.98-1.12, B = 256 0.95-1.06; 16-32 tiles per CU and any number 0.83-1.07.  64K
+// tokens, 8/2 heads, B = 64, top-24: 2062 -> 1800 us.
+bool hist_persist(const Problem& p) {
+  const int64_t nbins = (int64_t)p.Hkv * p.nblk_total;
+  return p.B <= 192 && p.hist_entries >= 64 * kCus * (int64_t)kRows &&
+         p.hist_entries >= nbins * (p.B <= 64 ? 1024 : 2048);
+}
+
 }  // namespace
 
 // Restrict-qualified copies of the tables: uniform loads from them are scalar.
@@ -353,7 +534,12 @@ void attn_mfma_kernel(AttnArgs a, Problem p, uint32_t ncur, uint32_t first,
 
 hipError_t launch_attn_hist_bf16(const AttnArgs& a, const Problem& p, int64_t tiles, hipStream_t st) {
   if (tiles <= 0) return hipSuccess;
-  const int64_t grid = (tiles + 7) / 8 * 8;
+  int64_t grid = (tiles + 7) / 8 * 8;
+  if (hist_persist(p)) {
+    grid = std::min<int64_t>(grid, kCus);
+    attn_hist_persist_kernel<<<(unsigned)grid, 512, 0, st>>>(a, p);
+    return hipGetLastError();
+  }
   attn_mfma_kernel<kHist, 8><<<(unsigned)grid, 512, 0, st>>>(a, p, 0, 0, MOBA_ATTN_TABLES(a));
   return hipGetLastError();
 }
@@ -370,7 +556,7 @@ hipError_t launch_attn_causal_bf16(bool dense, const AttnArgs& a, const Problem&
   });
 }
 
-bool attn_bf16_joint(const Problem& p) { return p.B <= kJointMaxBlock; }
+bool attn_bf16_joint(const Problem& p) { return p.B <= kJointMaxBlock && !hist_persist(p); }
 
 hipError_t launch_attn_joint_bf16(const AttnArgs& a, const Problem& p, int64_t hist_tiles,
                                   bool in_place, hipStream_t st) {

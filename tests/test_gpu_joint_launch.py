@@ -61,3 +61,21 @@ def test_smallest_workspace(monkeypatch):
     for limit in (hi, hi + 2048, hi + 8192, hi + 65536):
         out, lse = run(limit)
         assert torch.equal(out, ref) and torch.equal(lse, rlse)
+
+
+@pytest.mark.parametrize("seqlens,hq,hkv,B,topk", [
+    ((8192, 8197), 32, 2, 16, 12),     # one key tile per history tile
+    ((6000, 5, 11000), 32, 2, 48, 12),  # blocks across two key tiles
+    ((14000, 14900), 32, 2, 100, 8),
+])
+def test_persistent_history(seqlens, hq, hkv, B, topk):
+    """Batches large enough for the persistent history kernel; alone, their sequences
+    are not: the same bits."""
+    q, k, v, cu = inputs.make(seqlens, hq, hkv, 128, torch.bfloat16, B, 0.5, B, device=DEV)
+    entries = [binding.route_size(inputs.cu_seqlens((L,)), B, topk, hq)[1] for L in seqlens]
+    assert sum(entries) >= 64 * 256 * 256 * 1.1 > 1.1 * max(entries)
+    out, lse = binding.forward(q, k, v, cu, B, topk)
+    for s, L in enumerate(seqlens):
+        a, b = int(cu[s]), int(cu[s + 1])
+        o, l = binding.forward(q[a:b], k[a:b], v[a:b], inputs.cu_seqlens((L,)), B, topk)
+        assert torch.equal(o, out[a:b]) and torch.equal(l, lse[:, a:b])
