@@ -236,7 +236,8 @@ void attn_mfma_kernel(AttnArgs a, Problem p, uint32_t ncur, uint32_t first,
       y = (int)bx;
       g = a.g0 + blockIdx.y;
     } else {
-      const TileAt at = causal_at(bx, a.nhead, a.ntiles, (uint32_t)(a.g1 - a.g0), kSubTiles,
+      const TileAt at =
+          causal_at<MODE == kCur>(bx, a.nhead, a.ntiles, (uint32_t)(a.g1 - a.g0), kSubTiles,
                                   MODE == kJoint ? block_parts(p) : 1);
       y = at.tile;
       g = a.g0 + at.g;

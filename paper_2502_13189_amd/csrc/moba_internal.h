@@ -179,31 +179,40 @@ __device__ __forceinline__ int routed_slots(const SeqInfo& sq, const Problem& p,
 // Work-group x of a forward launch over the causal tiles of nkv kv-heads: the kv-head
 // (from the launch's first), the tile of the list and which part of it.  sh and sb
 // work-groups (1 or 2) per head-block and single-block tile.  8 consecutive tiles of the
-// list sit on the 8 XCDs, the work-groups of a tile follow each other on its XCD.  The
-// head blocks' tiles come first, each rank of the list for all kv-heads before the next:
-// they are up to topk blocks long, and one of the last kv-head that starts when the others
-// are done holds up the launch (current-block launch of 16384 tokens, 32/32 heads, B = 2049,
-// top-3: 582 us, one kv-head after the other 770; 24000 tokens, 16/16, B = 3000, top-5: 978 and
-// 1109).  A single block's tiles stay together, sharing K and V in their XCD's L2.
+// list sit on the 8 XCDs, the work-groups of a tile follow each other on its XCD, a single
+// block's tiles stay together, sharing K and V in their XCD's L2.
+// BY_RANK: the head blocks' tiles first, each rank of the list for all kv-heads before
+// the next: they are up to topk blocks long, and one of the last kv-head that starts when
+// the others are done holds up the launch (current-block launch of 16384 tokens, 32/32 heads,
+// B = 2049, top-3: 582 us, one kv-head after the other 624-770; 24000 tokens, 16/16, B =
+// 3000, top-5: 978 and 1109).  Otherwise one kv-head after the other, its head blocks first:
+// where history tiles follow in the launch and fill its end (8192 tokens, 32 heads, B =
+// 512, top-3: 233 us, by rank 239).
 struct TileAt {
   int g, tile, sub;
 };
 
+template <bool BY_RANK>
 __device__ __forceinline__ TileAt causal_at(uint32_t x, int64_t nhead, int64_t ntiles, uint32_t nkv,
                                             uint32_t sh, uint32_t sb) {
-  const uint32_t nx = (uint32_t)nhead * sh * nkv;
+  const uint32_t nh = (uint32_t)nhead * sh, nb = (uint32_t)(ntiles - nhead) * sb;
   TileAt r;
-  if (x < nx) {
-    const uint32_t z = x / (8 * sh), y = x % (8 * sh);
-    r.g = (int)(z % nkv);
-    r.tile = (int)(z / nkv * 8 + y % 8);
-    r.sub = (int)(y / 8);
+  uint32_t z;
+  bool head;
+  if constexpr (BY_RANK) {
+    head = x < nh * nkv;
+    const uint32_t y = x / (8 * sh);
+    r.g = (int)(head ? y % nkv : (x - nh * nkv) / nb);
+    z = head ? y / nkv * (8 * sh) + x % (8 * sh) : (x - nh * nkv) % nb;
   } else {
-    const uint32_t per = (uint32_t)(ntiles - nhead) * sb, z = (x - nx) % per;
-    r.g = (int)((x - nx) / per);
-    r.tile = (int)(nhead + (sb == 1 ? z : z / 16 * 8 + z % 8));
-    r.sub = (int)(sb == 1 ? 0 : z / 8 % 2);
+    r.g = (int)(x / (nh + nb));
+    z = x % (nh + nb);
+    head = z < nh;
+    z -= head ? 0 : nh;
   }
+  const uint32_t s = head ? sh : sb, first = head ? 0 : (uint32_t)nhead;
+  r.tile = (int)(first + (s == 1 ? z : z / 16 * 8 + z % 8));
+  r.sub = (int)(s == 1 ? 0 : z / 8 % 2);
   return r;
 }
 
