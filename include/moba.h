@@ -105,6 +105,8 @@ typedef enum {
  * topk is at least the block count of the longest sequence, every row
  * attends its whole causal prefix and the call runs moba_dense_forward's
  * kernels (the same result up to rounding).
+ * A row whose gate scores are not all finite has no defined selection, so its
+ * results are unspecified; it changes no other row's.
  *
  * Arguments: see the conventions above.  block_size >= 1, topk >= 1.
  * Returns MOBA_OK or an error status; on error nothing has been enqueued
@@ -335,7 +337,7 @@ const char* moba_status_string(moba_status status);
  * it returns the number of phases written.
  */
 typedef struct {
-  char name[24];     /* "pool", "vt_pack", "gate", "route", "attn_hist", ... */
+  char name[24];     /* "pool", "gate", "route", "attn_hist", "merge", ... */
   int64_t launches;  /* phase executions recorded */
   double total_ms;   /* summed event-to-event time */
 } moba_phase_stat;
