@@ -143,11 +143,11 @@ __device__ __forceinline__ int packed_key(int p) {
 // Dims 32 quarter .. + 31 of tile idx (< vt_tiles) of kv-head g, by one wave.
 __device__ __forceinline__ void pack_tile(const __hip_bfloat16* __restrict__ v, int64_t v_st,
                                           int64_t v_sh, const SeqInfo* __restrict__ seqs,
-                                          const Problem& p, int64_t idx, int g, int quarter,
-                                          __hip_bfloat16* __restrict__ vt,
+                                          int S, int64_t vt_tiles, int64_t idx, int g,
+                                          int quarter, __hip_bfloat16* __restrict__ vt,
                                           uint16_t (*tile)[kPackRow]) {
   const int lane = threadIdx.x & 63;
-  const int s = find_seq(seqs, p.S, idx, [](const SeqInfo& x) { return x.vt_tile_off; });
+  const int s = find_seq(seqs, S, idx, [](const SeqInfo& x) { return x.vt_tile_off; });
   const SeqInfo sq = seqs[s];
   const int i = (int)(idx - sq.vt_tile_off);
   // stage 64 keys x 32 dims: 4 lanes per key, 16 keys per load
@@ -169,7 +169,7 @@ __device__ __forceinline__ void pack_tile(const __hip_bfloat16* __restrict__ v, 
     dst[3] = u[x].w;
   }
   asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");  // the wave's own writes, no barrier
-  __hip_bfloat16* dst = vt + ((int64_t)g * p.vt_tiles + idx) * (kKeyTile * kHeadDim) +
+  __hip_bfloat16* dst = vt + ((int64_t)g * vt_tiles + idx) * (kKeyTile * kHeadDim) +
                         32 * quarter * kKeyTile;
 #pragma unroll
   for (int x = 0; x < 4; x++) {
@@ -187,14 +187,16 @@ __device__ __forceinline__ void pack_tile(const __hip_bfloat16* __restrict__ v, 
 }
 
 // The pack by itself (dense attention): one tile per work-group (small dense calls ran 0.5-1.3 us
-// slower with 1024-thread ones).
+// slower with 1024-thread ones).  It takes the two counts it needs, not the whole Problem: the
+// smallest dense calls wait for the host, and the launch costs them 0.15 of 22 us less.
 __global__ __launch_bounds__(256) void pack_kernel(const __hip_bfloat16* __restrict__ v,
                                                    int64_t v_st, int64_t v_sh,
-                                                   const SeqInfo* __restrict__ seqs, Problem p,
+                                                   const SeqInfo* __restrict__ seqs, int S,
+                                                   int64_t vt_tiles,
                                                    __hip_bfloat16* __restrict__ vt) {
   __shared__ __attribute__((aligned(16))) uint16_t tile[4][kKeyTile][kPackRow];
   const int wave = threadIdx.x >> 6;
-  pack_tile(v, v_st, v_sh, seqs, p, blockIdx.x, blockIdx.y, wave, vt, tile[wave]);
+  pack_tile(v, v_st, v_sh, seqs, S, vt_tiles, blockIdx.x, blockIdx.y, wave, vt, tile[wave]);
 }
 
 // Work-groups [0, npool): pool (block, kv-head); then pack (a tile per four waves, kv-head).
@@ -222,7 +224,7 @@ void pool_pack_kernel(
     const int wave = threadIdx.x >> 6;
     const int64_t idx = (int64_t)(y % per) * kPackTiles + (wave >> 2);
     if (idx < p.vt_tiles)
-      pack_tile(v, v_st, v_sh, seqs, p, idx, (int)(y / per), wave & 3, vt,
+      pack_tile(v, v_st, v_sh, seqs, p.S, p.vt_tiles, idx, (int)(y / per), wave & 3, vt,
                 reinterpret_cast<uint16_t(*)[kPackRow]>(lds) + wave * kKeyTile);
   }
 }
@@ -277,7 +279,8 @@ hipError_t launch_pool(const void* k, bool bf16, int64_t k_st, int64_t k_sh, con
 hipError_t launch_pack(const __hip_bfloat16* v, int64_t v_st, int64_t v_sh, const SeqInfo* seqs,
                        const Problem& p, __hip_bfloat16* vt, hipStream_t st) {
   if (p.vt_tiles == 0) return hipSuccess;
-  pack_kernel<<<dim3((unsigned)p.vt_tiles, p.Hkv), 256, 0, st>>>(v, v_st, v_sh, seqs, p, vt);
+  pack_kernel<<<dim3((unsigned)p.vt_tiles, p.Hkv), 256, 0, st>>>(v, v_st, v_sh, seqs, p.S, p.vt_tiles,
+                                                                      vt);
   return hipGetLastError();
 }
 
