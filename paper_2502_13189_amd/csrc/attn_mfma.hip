@@ -55,7 +55,8 @@
 namespace moba {
 namespace {
 
-enum { kHist = 0, kCur = 1, kDense = 2, kJoint = 3 };
+// kCur, kCurSeq: the current-block launch in the two orders of causal_at
+enum { kHist = 0, kCur = 1, kDense = 2, kJoint = 3, kCurSeq = 4 };
 
 constexpr int kRows = kTileRowsMfma;               // query rows per plan tile (256)
 constexpr int kLdsChunks = 2 * kBufK + 2 * kBufV;  // 70 KiB: two K and two V^T buffers
@@ -68,6 +69,10 @@ constexpr float kSumLimit = 256.0f;  // largest per-lane weight sum kept without
 // kernel (see hist_persist).  Both launches' time, 8-wave then 4-wave: B = 512,
 // 8K tokens, 32 heads: 289 -> 260 us; B = 128, 1033 tokens, 8/2 heads: 22 -> 10 us; B =
 // 2048, 32K tokens, 32/8 heads: 2454 -> 2422 us; B = 4096, 1M tokens: 670 -> 698 ms.
+// Whole forwards of B = 2049-4096, the 8-wave launches' time by that of one joint launch:
+// 9K tokens 1.00-1.37, 16K 0.96-1.21 (mostly 1.02-1.11), 32K 0.97-1.18; 64K and more with
+// 4 heads per kv-head 0.97-1.01, one head each 0.97-1.11, the most for top-2.  So the line
+// could lie higher for short batches; long ones lose up to 3%.
 constexpr int kJointMaxBlock = 2048;
 constexpr int kCus = 256;
 constexpr float kLn2 = 0.69314718055994531f;
@@ -194,7 +199,7 @@ void attn_mfma_kernel(AttnArgs a, Problem p, uint32_t ncur, uint32_t first,
   const int qc = lane & 31, hh = lane >> 5;
 
   // ------------------------------------------------------------ tile setup
-  const uint32_t bx = MODE == kJoint || MODE == kCur ? first + blockIdx.x : blockIdx.x;
+  const uint32_t bx = MODE == kHist || MODE == kDense ? blockIdx.x : first + blockIdx.x;
   const bool hist = MODE == kHist || (MODE == kJoint && bx >= ncur);
   int g, s;
   int64_t kbeg, kend, tmin;
@@ -545,6 +550,16 @@ hipError_t launch_attn_hist_bf16(const AttnArgs& a, const Problem& p, int64_t ti
   return hipGetLastError();
 }
 
+// Whether the current-block launch takes its head tiles by rank (see causal_at): not where a
+// kv-head's block tiles, half a block long on average, keep the CUs busy for as long as the
+// longest head tile, topk blocks, lasts.  By rank, then kv-head by kv-head: 1M tokens, 32/8
+// heads, B = 4096, top-12: 52.4 -> 51.9 ms (24.6 -> 11.4 GB read per launch), 512K 33.95 ->
+// 33.6; below the line, 64K, 32/32, B = 2049, top-3: 1734 -> 1901 us, 128K, 16/16, B = 3000,
+// top-5: 2624 -> 2810.
+bool causal_by_rank(const AttnArgs& a, const Problem& p) {
+  return a.ntiles - a.nhead < 2 * kCus * (int64_t)p.topk;
+}
+
 hipError_t launch_attn_causal_bf16(bool dense, const AttnArgs& a, const Problem& p, hipStream_t st) {
   if (a.ntiles <= 0 || a.g1 <= a.g0) return hipSuccess;
   if (dense) {
@@ -552,8 +567,12 @@ hipError_t launch_attn_causal_bf16(bool dense, const AttnArgs& a, const Problem&
     attn_mfma_kernel<kDense, 8><<<grid, 512, 0, st>>>(a, p, 0, 0, MOBA_ATTN_TABLES(a));
     return hipGetLastError();
   }
+  const bool by_rank = causal_by_rank(a, p);
   return launch_pieces(a.ntiles * (a.g1 - a.g0), 512, [&](uint32_t first, unsigned n) {
-    attn_mfma_kernel<kCur, 8><<<n, 512, 0, st>>>(a, p, 0, first, MOBA_ATTN_TABLES(a));
+    if (by_rank)
+      attn_mfma_kernel<kCur, 8><<<n, 512, 0, st>>>(a, p, 0, first, MOBA_ATTN_TABLES(a));
+    else
+      attn_mfma_kernel<kCurSeq, 8><<<n, 512, 0, st>>>(a, p, 0, first, MOBA_ATTN_TABLES(a));
   });
 }
 

@@ -185,9 +185,10 @@ __device__ __forceinline__ int routed_slots(const SeqInfo& sq, const Problem& p,
 // the next: they are up to topk blocks long, and one of the last kv-head that starts when
 // the others are done holds up the launch (current-block launch of 16384 tokens, 32/32 heads,
 // B = 2049, top-3: 582 us, one kv-head after the other 624-770; 24000 tokens, 16/16, B =
-// 3000, top-5: 978 and 1109).  Otherwise one kv-head after the other, its head blocks first:
-// where history tiles follow in the launch and fill its end (8192 tokens, 32 heads, B =
-// 512, top-3: 233 us, by rank 239).
+// 3000, top-5: 978 and 1109).  Otherwise one kv-head after the other, its head blocks first,
+// which keeps a kv-head's K and V in the L2s: where history tiles follow in the launch and
+// fill its end (8192 tokens, 32 heads, B = 512, top-3: 233 us, by rank 239), or the last
+// kv-head's blocks do (causal_by_rank).
 struct TileAt {
   int g, tile, sub;
 };
