@@ -219,10 +219,11 @@ __global__ __launch_bounds__(256) void decode_gate_kernel(DecodeArgs a, Problem 
 
 // ================================================================ attend
 // GM: the group size rounded up to a power of two (sizes the LDS arrays, so
-// small groups leave room for more resident work-groups).  first: the launch's first
-// work-group (full attention).
+// small groups leave room for more resident work-groups).  near, first: full attention's
+// order (see full_heads_near) and the launch's first eight chunks.
 template <int GM>
-__global__ __launch_bounds__(256) void decode_attend_kernel(DecodeArgs a, Problem p, uint32_t first,
+__global__ __launch_bounds__(256) void decode_attend_kernel(DecodeArgs a, Problem p, bool near,
+                                                            uint32_t first,
                                                             const SeqInfo* __restrict__ seqs) {
   __shared__ __attribute__((aligned(16))) uint32_t pw[GM][kDecodeChunk / 2];
   __shared__ float red[4][GM][2];
@@ -235,12 +236,11 @@ __global__ __launch_bounds__(256) void decode_attend_kernel(DecodeArgs a, Proble
   const int G = p.G;
   int s, g, x;  // x: chunk id, block * nsub + piece
   if (a.full) {
-    // the grid runs over every sequence's chunks, a chunk's kv-heads next to each other
-    // (their rows are, too; kv-heads far apart read pieces of many rows at a time: 200
-    // sequences of 130 tokens, 32 kv-heads: 95 us, this way 78)
-    const uint32_t w = first + blockIdx.x, c = w / (uint32_t)p.Hkv;
+    // the grid runs over every sequence's chunks
+    const uint32_t c = near ? 8 * (first + blockIdx.y) + blockIdx.x % 8 : blockIdx.x;
+    if (c >= (uint32_t)p.nblk_total) return;
     s = find_seq(seqs, p.S, c, [](const SeqInfo& y) { return y.blk_off; });
-    g = (int)(w % (uint32_t)p.Hkv);
+    g = (int)(near ? blockIdx.x / 8 : blockIdx.y);
     x = (int)c - seqs[s].blk_off;
   } else {
     s = blockIdx.y / p.Hkv;
@@ -600,20 +600,43 @@ hipError_t launch_decode_gate(const DecodeArgs& a, const Problem& p, hipStream_t
   return hipGetLastError();
 }
 
+// Full attention: the kv-heads of eight chunks (one on each XCD) before the next eight.
+// A token's rows of all kv-heads lie side by side, so memory, and each XCD's address
+// translation, then go through the cache once; one kv-head after the other they go
+// through it Hkv times.  Calls, one after the other -> this way: 1M tokens, 8 kv-heads 850 ->
+// 802 us; 300K, 4 kv-heads 123 -> 118; 65536, 32 kv-heads 251 -> 187; 200 sequences of 130
+// tokens, 32 kv-heads 105 -> 89.  A cache of up to about the 256 MB last-level cache, read
+// again by the next call, was the faster one the other way: 127K tokens, 4 kv-heads (260 MB)
+// 45.5 and 48.7; 65536, 8 kv-heads (268 MB) 49.1 and 51.4; 20000, 32 kv-heads (327 MB) 61.6
+// and 60.7.  The line lies between (counted in whole chunks).
+bool full_heads_near(const Problem& p) {
+  constexpr int64_t kChunkBytes = 2 * 2 * kHeadDim * kDecodeChunk;
+  return (int64_t)p.nblk_total * p.Hkv * kChunkBytes > (int64_t(300) << 20);
+}
+
 hipError_t launch_decode_attend(const DecodeArgs& a, const Problem& p, hipStream_t st) {
   if (p.S <= 0 || a.nchunk <= 0) return hipSuccess;
+  const bool near = a.full && full_heads_near(p);
   const auto run = [&](dim3 grid, uint32_t first) {
-    if (p.G <= 1) decode_attend_kernel<1><<<grid, 256, 0, st>>>(a, p, first, a.seqs);
-    else if (p.G <= 2) decode_attend_kernel<2><<<grid, 256, 0, st>>>(a, p, first, a.seqs);
-    else if (p.G <= 4) decode_attend_kernel<4><<<grid, 256, 0, st>>>(a, p, first, a.seqs);
-    else if (p.G <= 8) decode_attend_kernel<8><<<grid, 256, 0, st>>>(a, p, first, a.seqs);
-    else decode_attend_kernel<kDecodeMaxGroup><<<grid, 256, 0, st>>>(a, p, first, a.seqs);
+    if (p.G <= 1) decode_attend_kernel<1><<<grid, 256, 0, st>>>(a, p, near, first, a.seqs);
+    else if (p.G <= 2) decode_attend_kernel<2><<<grid, 256, 0, st>>>(a, p, near, first, a.seqs);
+    else if (p.G <= 4) decode_attend_kernel<4><<<grid, 256, 0, st>>>(a, p, near, first, a.seqs);
+    else if (p.G <= 8) decode_attend_kernel<8><<<grid, 256, 0, st>>>(a, p, near, first, a.seqs);
+    else decode_attend_kernel<kDecodeMaxGroup><<<grid, 256, 0, st>>>(a, p, near, first, a.seqs);
   };
   // full: every sequence's chunks (the plan's blocks are chunks then); MoBA: slots
-  if (a.full)
-    return launch_pieces((int64_t)p.nblk_total * p.Hkv, 256,
-                         [&](uint32_t first, unsigned n) { run(dim3(n), first); });
-  run(dim3((unsigned)(a.nunion * a.nsub), (unsigned)(p.S * p.Hkv)), 0);
+  if (near) {
+    constexpr int64_t kMost = 65535;  // of a grid's second dimension
+    const int64_t eights = ((int64_t)p.nblk_total + 7) / 8;
+    for (int64_t first = 0; first < eights; first += kMost) {
+      run(dim3(8 * (unsigned)p.Hkv, (unsigned)std::min(kMost, eights - first)), (uint32_t)first);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
+  run(a.full ? dim3((unsigned)p.nblk_total, (unsigned)p.Hkv)
+             : dim3((unsigned)(a.nunion * a.nsub), (unsigned)(p.S * p.Hkv)), 0);
   return hipGetLastError();
 }
 

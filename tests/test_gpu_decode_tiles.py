@@ -29,6 +29,9 @@ def _need_gpu():
     ((2060, 300), 1, 1, 2, 12),                   # 1030 blocks: selection by argmax rounds
     ((513, 521, 1025, 1033, 2571), 2, 1, 8, 5),   # 64, 65, 128, 129, 321 past blocks: passes of 64 to 256
     ((17000,), 8, 1, 64, 64),                     # one combine share of 64 slots
+    # full attention's two orders: 75 and 77 chunks of 32 kv-heads, either side of the line
+    ((7,) * 75, 32, 32, 16, 3),
+    ((7,) * 70 + (1300, 40), 32, 32, 16, 3),
 ])
 @pytest.mark.parametrize("mode", ["moba", "full"])
 def test_decode_tiles(seqlens, hq, hkv, B, topk, mode):
